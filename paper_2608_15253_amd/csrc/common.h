@@ -14,7 +14,7 @@ constexpr double kKB = 1.380649e-23;
 constexpr double kHbar = 6.62607015e-34 / (2.0 * kPi);  // exact SI h / 2 pi
 constexpr double kQe = 1.602176634e-19;                 // exact SI elementary charge
 
-constexpr int kMaxPass = 16;
+constexpr int kMaxPass = 6;
 constexpr int kTensorStride = 8;  // reals per frequency of the tensor spectrum
 
 // aligned to its size, so that a complex value in LDS moves as one 8-byte
@@ -49,13 +49,30 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Stockham plan of one transform length: radices applied in order; `prune`
-// marks a first radix-2 pass whose upper half input is known to be zero.
+// t / d for 0 <= t, t d < 2^31, with the host-computed m = magic_of(d) =
+// ceil(2^31 / d): one multiply instead of the thirty-odd instructions of an
+// integer division, and no special case for d = 1
+__host__ __device__ inline unsigned magic_of(int d) {
+  return (unsigned)((0x80000000ull + (unsigned)d - 1) / (unsigned)d);
+}
+__device__ inline int mdiv(int t, unsigned m) { return (int)__umulhi((unsigned)t << 1, m); }
+
+// One pass of a Stockham plan: radix R, nb = n / R butterflies per line, Ns
+// the product of the earlier radices, off the pass's first twiddle in the
+// pass-ordered table, the magics of nb and Ns.
+struct FftPass {
+  int R, nb, Ns, off;
+  unsigned mnb, mNs;
+};
+
+// Stockham plan of one transform length: passes applied in order; `prune`
+// marks a line whose upper half input is known to be zero (never read; the
+// first radix is then even).
 struct FftPlan {
   int n;
   int npass;
   int prune;
-  int radix[kMaxPass];
+  FftPass ps[kMaxPass];
 };
 
 }  // namespace mmx

@@ -5,10 +5,18 @@
 // inputs of a butterfly at stride n/R, applies the Stockham twiddles
 // exp(-+2 pi i r (j mod Ns) / (Ns R)), transforms them with a small DFT and
 // writes them to the autosorted position (j / Ns) Ns R + (j mod Ns) + r Ns of
-// the other buffer; Ns grows by R per pass, so mixed radices 2, 3, 4, 5, 8 and
-// 16 combine in any order and the output is in natural order.  A pruned first
-// pass (radix 2, input zero beyond n/2, as in the zero-padded demag
-// convolution) reduces to duplicating its input.  Transforms are unnormalised.
+// the other buffer; Ns grows by R per pass, so mixed radices combine in any
+// order and the output is in natural order.  The first pass (Ns = 1) has no
+// twiddles; the others read theirs from a pass-ordered table, the R - 1
+// factors of a butterfly adjacent.  A pruned first pass (input zero beyond
+// n/2, as in the zero-padded demag convolution) reads the lower half only.
+// Transforms are unnormalised.
+//
+// What bounds these passes is the number of instructions a wave issues: a
+// grid of one replica leaves one or two waves per SIMD, which issue one
+// instruction in about 8 cycles (3.4 ns), so index arithmetic costs as much
+// as butterflies.  Line and position come from multiplications by host-computed
+// reciprocals, twiddles from consecutive table entries.
 #pragma once
 #include "common.h"
 
@@ -139,6 +147,7 @@ struct Dft {
       for (int n1 = 0; n1 < A; ++n1) t[n1] = v[B * n1 + n2];
       if constexpr (A == 3) r3(t);
       if constexpr (A == 4) r4(t);
+      if constexpr (A == 5) r5(t);
 #pragma unroll
       for (int k1 = 0; k1 < A; ++k1) {
         const int j = n2 * k1;
@@ -151,10 +160,32 @@ struct Dft {
       cpx<T> t[B];
 #pragma unroll
       for (int n2 = 0; n2 < B; ++n2) t[n2] = a[n2][k1];
+      if constexpr (B == 2) r2(t);
+      if constexpr (B == 3) r3(t);
       if constexpr (B == 8) r8(t);
 #pragma unroll
       for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = t[k2];
     }
+  }
+  // 6-, 9- and 10-point DFTs as 3 x 2, 3 x 3 and 5 x 2
+  static __device__ inline void r6(cpx<T>* v) {
+    const T h = T(0.86602540378443864676);
+    const T wc[3] = {T(1), T(0.5), T(-0.5)}, ws[3] = {T(0), h, h};
+    split<3, 2>(v, wc, ws);
+  }
+  static __device__ inline void r9(cpx<T>* v) {
+    const T wc[5] = {T(1), T(0.76604444311897803520), T(0.17364817766693034885), T(-0.5),
+                     T(-0.93969262078590838405)};
+    const T ws[5] = {T(0), T(0.64278760968653932632), T(0.98480775301220805937),
+                     T(0.86602540378443864676), T(0.34202014332566873304)};
+    split<3, 3>(v, wc, ws);
+  }
+  static __device__ inline void r10(cpx<T>* v) {
+    const T wc[5] = {T(1), T(0.80901699437494742410), T(0.30901699437494742410),
+                     T(-0.30901699437494742410), T(-0.80901699437494742410)};
+    const T ws[5] = {T(0), T(0.58778525229247312917), T(0.95105651629515357212),
+                     T(0.95105651629515357212), T(0.58778525229247312917)};
+    split<5, 2>(v, wc, ws);
   }
   // 24-point DFT as 3 x 8
   static __device__ inline void r24(cpx<T>* v) {
@@ -198,85 +229,183 @@ struct Dft {
   }
 };
 
-template <typename T, bool INV, int R>
+// One pass; FIRST: Ns = 1, no twiddles; HALF: inputs j + r nb with r >= R/2
+// are zero and not read.
+template <typename T, bool INV, int R, bool FIRST, bool HALF>
 __device__ inline void stockham_pass(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
-                                     int n, int Ns, int nlines, const cpx<T>* __restrict__ tw,
+                                     const FftPass& p, int nlines, const cpx<T>* __restrict__ tw,
                                      int tid, int nthr, int ld) {
-  const int nb = n / R;
+  static_assert(!HALF || (FIRST && R % 2 == 0), "pruned first pass");
+  const int nb = p.nb, Ns = p.Ns;
   const int total = nb * nlines;
-  const int twscale = n / (Ns * R);
-  // power-of-two extents (the common case) index with shifts and masks
-  const bool p2 = ((nb & (nb - 1)) == 0) && ((Ns & (Ns - 1)) == 0);
-  const int lnb = __builtin_ctz(nb), lns = __builtin_ctz(Ns);
   for (int t = tid; t < total; t += nthr) {
-    const int line = p2 ? (t >> lnb) : t / nb;
+    const int line = mdiv(t, p.mnb);
     const int j = t - line * nb;
-    const cpx<T>* s = src + line * ld;
-    cpx<T>* d = dst + line * ld;
-    const int jq = p2 ? (j >> lns) : j / Ns;
-    const int jm = j - jq * Ns;
+    const cpx<T>* s = src + line * ld + j;
     cpx<T> v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = s[j + r * nb];
-    if (jm != 0) {
+    for (int r = 0; r < R; ++r) v[r] = (HALF && r >= R / 2) ? cpx<T>{0, 0} : s[r * nb];
+    int o = j;  // (j / Ns) Ns R + (j mod Ns)
+    if constexpr (FIRST) {
+      o = j * R;
+    } else {
+      const int jq = mdiv(j, p.mNs);
+      const cpx<T>* w = tw + p.off + (j - jq * Ns) * (R - 1);
 #pragma unroll
-      for (int r = 1; r < R; ++r) {
-        const cpx<T> w = tw[r * jm * twscale];
-        v[r] = INV ? cmulc(v[r], w) : cmul(v[r], w);
-      }
+      for (int r = 1; r < R; ++r) v[r] = INV ? cmulc(v[r], w[r - 1]) : cmul(v[r], w[r - 1]);
+      o += jq * (Ns * (R - 1));
     }
     if constexpr (R == 2) Dft<T, INV>::r2(v);
     if constexpr (R == 3) Dft<T, INV>::r3(v);
     if constexpr (R == 4) Dft<T, INV>::r4(v);
     if constexpr (R == 5) Dft<T, INV>::r5(v);
+    if constexpr (R == 6) Dft<T, INV>::r6(v);
     if constexpr (R == 8) Dft<T, INV>::r8(v);
-    if constexpr (R == 16) Dft<T, INV>::r16(v);
-    const int idxD = jq * Ns * R + jm;
+    if constexpr (R == 9) Dft<T, INV>::r9(v);
+    if constexpr (R == 10) Dft<T, INV>::r10(v);
+    cpx<T>* d = dst + line * ld + o;
 #pragma unroll
-    for (int r = 0; r < R; ++r) d[idxD + r * Ns] = v[r];
+    for (int r = 0; r < R; ++r) d[FIRST ? r : r * Ns] = v[r];
   }
 }
 
 // Transforms nlines lines in `a` (scratch `b`), returns the buffer holding the
-// result.  `tw` is the table exp(-2 pi i k / n), k < n.  Lines start every
-// `ld` slots (0: every n, contiguous).  Must be called by the whole
+// result.  `tw` is the plan's pass-ordered table (plan_twiddles).  Lines start
+// every `ld` slots (0: every n, contiguous).  Must be called by the whole
 // workgroup; ends with a barrier.
 template <typename T, bool INV>
 __device__ cpx<T>* lds_fft(cpx<T>* a, cpx<T>* b, int nlines, const FftPlan& p,
                            const cpx<T>* __restrict__ tw, int ld = 0) {
-  const int n = p.n;
-  if (ld == 0) ld = n;
+  if (p.npass == 0) return a;
+  if (ld == 0) ld = p.n;
   const int tid = threadIdx.x, nthr = blockDim.x;
-  int Ns = 1;
-  for (int ps = 0; ps < p.npass; ++ps) {
-    const int R = p.radix[ps];
-    if (ps == 0 && p.prune) {
-      const int half = n / 2;
-      const int total = half * nlines;
-      for (int t = tid; t < total; t += nthr) {
-        const int line = udiv(t, half);
-        const int j = t - line * half;
-        const cpx<T> v = a[line * ld + j];
-        b[line * ld + 2 * j] = v;
-        b[line * ld + 2 * j + 1] = v;
+#define MMX_PASS(R, FIRST, HALF) \
+  stockham_pass<T, INV, R, FIRST, HALF>(a, b, ps, nlines, tw, tid, nthr, ld)
+  {
+    const FftPass& ps = p.ps[0];
+    if (!INV && p.prune) {
+      switch (ps.R) {
+        case 2: MMX_PASS(2, true, !INV); break;
+        case 4: MMX_PASS(4, true, !INV); break;
+        case 6: MMX_PASS(6, true, !INV); break;
+        case 8: MMX_PASS(8, true, !INV); break;
+        default: MMX_PASS(10, true, !INV); break;
       }
     } else {
-      switch (R) {
-        case 2: stockham_pass<T, INV, 2>(a, b, n, Ns, nlines, tw, tid, nthr, ld); break;
-        case 3: stockham_pass<T, INV, 3>(a, b, n, Ns, nlines, tw, tid, nthr, ld); break;
-        case 4: stockham_pass<T, INV, 4>(a, b, n, Ns, nlines, tw, tid, nthr, ld); break;
-        case 5: stockham_pass<T, INV, 5>(a, b, n, Ns, nlines, tw, tid, nthr, ld); break;
-        case 8: stockham_pass<T, INV, 8>(a, b, n, Ns, nlines, tw, tid, nthr, ld); break;
-        default: stockham_pass<T, INV, 16>(a, b, n, Ns, nlines, tw, tid, nthr, ld); break;
+      switch (ps.R) {
+        case 2: MMX_PASS(2, true, false); break;
+        case 3: MMX_PASS(3, true, false); break;
+        case 4: MMX_PASS(4, true, false); break;
+        case 5: MMX_PASS(5, true, false); break;
+        case 6: MMX_PASS(6, true, false); break;
+        case 8: MMX_PASS(8, true, false); break;
+        case 9: MMX_PASS(9, true, false); break;
+        default: MMX_PASS(10, true, false); break;
       }
     }
-    __syncthreads();
+  }
+  __syncthreads();
+  for (int i = 1; i < p.npass; ++i) {
+    const FftPass& ps = p.ps[i];
     cpx<T>* t = a;
     a = b;
     b = t;
-    Ns *= R;
+    switch (ps.R) {
+      case 2: MMX_PASS(2, false, false); break;
+      case 3: MMX_PASS(3, false, false); break;
+      case 4: MMX_PASS(4, false, false); break;
+      case 5: MMX_PASS(5, false, false); break;
+      case 6: MMX_PASS(6, false, false); break;
+      case 8: MMX_PASS(8, false, false); break;
+      case 9: MMX_PASS(9, false, false); break;
+      default: MMX_PASS(10, false, false); break;
+    }
+    __syncthreads();
   }
-  return a;
+#undef MMX_PASS
+  return b;
+}
+
+// ---------------------------------------------------------------------------
+// lines of a power of two known at compile time
+// ---------------------------------------------------------------------------
+// Line storage of an N-point line: with N = 0 (length known at run time only)
+// plain; otherwise one spare slot follows every 16, so that the strided writes
+// of the early passes (R, then R^2 slots apart) spread over the LDS banks.
+// Strides that are multiples of 16 stay constants: every read and write of a
+// butterfly is one base address plus an immediate offset.
+template <int N>
+struct Line {
+  static constexpr int LD = N + N / 16;  // slots per line
+  static __device__ inline int at(int i) { return N ? i + (i >> 4) : i; }
+};
+
+// Radices of the fixed plan of N = 2^k >= 16 points, REST = N over the radices
+// already applied: eights, then fours; 64 points as three fours (their
+// butterflies keep twice the lanes busy).  make_plan uses the same ones, so
+// both read the same twiddle table.
+constexpr int fixed_radix(int n, int rest) {
+  return (n == 64 || rest == 16 || rest == 4) ? 4 : 8;
+}
+
+template <typename T, bool INV, int N, int REST, bool HALF>
+__device__ inline cpx<T>* fixed_passes(cpx<T>* a, cpx<T>* b, int nlines,
+                                       const cpx<T>* __restrict__ tw) {
+  constexpr int R = fixed_radix(N, REST), Ns = N / REST, nb = N / R;
+  constexpr bool FIRST = Ns == 1;
+  constexpr int LD = Line<N>::LD;
+  const int total = nb * nlines;
+  for (int t = threadIdx.x; t < total; t += blockDim.x) {
+    const int line = t / nb, j = t % nb;
+    const int jm = j % Ns, o = j + (j / Ns) * (Ns * (R - 1));
+    cpx<T> v[R];
+    if constexpr (nb % 16 == 0) {
+      const cpx<T>* s = a + line * LD + Line<N>::at(j);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        v[r] = (HALF && FIRST && r >= R / 2) ? cpx<T>{0, 0} : s[r * (nb + nb / 16)];
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        v[r] = (HALF && FIRST && r >= R / 2) ? cpx<T>{0, 0}
+                                             : a[line * LD + Line<N>::at(j + r * nb)];
+    }
+    if constexpr (!FIRST) {
+      // the earlier passes hold (Ns - 1) twiddles minus the first pass's
+      const cpx<T>* w = tw + (Ns - fixed_radix(N, N)) + jm * (R - 1);
+#pragma unroll
+      for (int r = 1; r < R; ++r) v[r] = INV ? cmulc(v[r], w[r - 1]) : cmul(v[r], w[r - 1]);
+    }
+    if constexpr (R == 4) Dft<T, INV>::r4(v);
+    if constexpr (R == 8) Dft<T, INV>::r8(v);
+    cpx<T>* d = b + line * LD;
+    if constexpr (Ns % 16 == 0) {
+      d += Line<N>::at(o);
+#pragma unroll
+      for (int r = 0; r < R; ++r) d[r * (Ns + Ns / 16)] = v[r];
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) d[Line<N>::at(o + r * Ns)] = v[r];
+    }
+  }
+  __syncthreads();
+  if constexpr (REST / R > 1)
+    return fixed_passes<T, INV, N, REST / R, HALF>(b, a, nlines, tw);
+  else
+    return b;
+}
+
+// Transforms of nlines lines held as Line<N> in `a` (scratch `b`); N = 0: of
+// the plan's length, contiguous.  HALF as the plan's prune.
+template <typename T, bool INV, int N>
+__device__ inline cpx<T>* line_fft(cpx<T>* a, cpx<T>* b, int nlines, const FftPlan& p,
+                                   const cpx<T>* __restrict__ tw) {
+  if constexpr (N == 0) {
+    return lds_fft<T, INV>(a, b, nlines, p, tw);
+  } else {
+    if (!INV && p.prune) return fixed_passes<T, INV, N, N, true>(a, b, nlines, tw);
+    return fixed_passes<T, INV, N, N, false>(a, b, nlines, tw);
+  }
 }
 
 }  // namespace mmx

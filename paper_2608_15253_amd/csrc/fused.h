@@ -27,7 +27,7 @@ template <typename T>
 struct HeunFusedArgs {
   FArgs<T> f;           // geometry, coefficients, thermal keys, tables
   FftPlan pxf, pxi, pyf, pyi;
-  const cpx<T>* tw_x;
+  const cpx<T>* tw_x;   // pass-ordered tables
   const cpx<T>* wpost;
   const cpx<T>* tw_y;
   const T* Nt;          // [Ty][Kx][kTensorStride], 2-D: xx, yy, zz, xy used

@@ -56,28 +56,73 @@ mmx_status fail(mmx_status s, const std::string& msg) {
 // ---------------------------------------------------------------------------
 // FFT planning
 // ---------------------------------------------------------------------------
+// Radices of a line of n points.  Costs are the instructions of one butterfly
+// (index arithmetic, LDS reads and writes, twiddles, the DFT) as counted in
+// the gfx950 code; a pass counts twice: once as the latency of a workgroup
+// whose threads hold about four points each (R > 4 then takes R / 4 threads'
+// work per thread) and once as throughput per point.  4 x 4 x 4 x 4 against 8 x 8
+// x 4 for 256 points is a draw, 2 x 3 x 3 x 5 for 90 is clearly worse than
+// 10 x 9.  Depends on n alone, so that every grouping of lines gives the same bits.
+constexpr int kRadices[] = {2, 3, 4, 5, 6, 8, 9, 10};
+constexpr int kRadixCost[] = {52, 73, 82, 115, 128, 166, 230, 220};
+
+double plan_search(int rest, bool even_first, std::vector<int>& cur, double cost, double best,
+                   std::vector<int>& out) {
+  if (rest == 1) {
+    if (cost < best) {
+      out = cur;
+      return cost;
+    }
+    return best;
+  }
+  if ((int)cur.size() == kMaxPass) return best;
+  for (int i = 7; i >= 0; --i) {
+    const int R = kRadices[i];
+    if (rest % R) continue;
+    if (even_first) {
+      if (cur.empty() && (R & 1)) continue;
+      if (cur.size() > 1 && R > cur.back()) continue;  // order: the first, then descending
+    } else if (!cur.empty() && R > cur.back()) {
+      continue;
+    }
+    const double c = kRadixCost[i] * (std::max(1.0, R / 4.0) + 4.0 / R);
+    if (cost + c >= best) continue;
+    cur.push_back(R);
+    best = plan_search(rest / R, even_first, cur, cost + c, best, out);
+    cur.pop_back();
+  }
+  return best;
+}
+
 bool make_plan(int n, bool prune, FftPlan& p) {
   std::memset(&p, 0, sizeof(p));
   p.n = n;
   if (n <= 1) return n == 1;
-  int rest = n;
-  if (prune) {
-    if (n % 2) return false;
-    p.radix[p.npass++] = 2;
-    p.prune = 1;
-    rest /= 2;
+  if (prune && n % 2) return false;
+  // an even length starts with an even radix, pruned or not, so that the
+  // forward and the inverse transform of an axis share their radices
+  std::vector<int> cur, R;
+  if (n >= 16 && (n & (n - 1)) == 0) {
+    for (int rest = n; rest > 1; rest /= fixed_radix(n, rest)) R.push_back(fixed_radix(n, rest));
+  } else {
+    plan_search(n, n % 2 == 0, cur, 0.0, 1e30, R);
   }
-  // radix 4 first: measured faster on gfx950 than 8/16 up to 256 points (the
-  // wider butterflies leave threads idle and write LDS with larger strides);
-  // from 512 points on, radix 8 first: fewer passes, and such lines are few
-  // per workgroup, so each pass's latency dominates (512x512 film RK45: 5 %
-  // faster in FP32, 6 % in FP64)
-  while (n >= 512 && rest % 8 == 0 && p.npass < kMaxPass) { p.radix[p.npass++] = 8; rest /= 8; }
-  while (rest % 4 == 0 && p.npass < kMaxPass) { p.radix[p.npass++] = 4; rest /= 4; }
-  while (rest % 2 == 0 && p.npass < kMaxPass) { p.radix[p.npass++] = 2; rest /= 2; }
-  while (rest % 3 == 0 && p.npass < kMaxPass) { p.radix[p.npass++] = 3; rest /= 3; }
-  while (rest % 5 == 0 && p.npass < kMaxPass) { p.radix[p.npass++] = 5; rest /= 5; }
-  return rest == 1;
+  if (R.empty() || (int)R.size() > kMaxPass) return false;
+  p.npass = (int)R.size();
+  p.prune = prune ? 1 : 0;
+  int Ns = 1, off = 0;
+  for (int i = 0; i < p.npass; ++i) {
+    FftPass& s = p.ps[i];
+    s.R = R[i];
+    s.nb = n / R[i];
+    s.Ns = Ns;
+    s.off = off;
+    s.mnb = magic_of(s.nb);
+    s.mNs = magic_of(Ns);
+    if (i > 0) off += Ns * (R[i] - 1);
+    Ns *= R[i];
+  }
+  return true;
 }
 
 bool fft_ok(int n) {
@@ -124,6 +169,25 @@ std::vector<cpx<T>> twiddles(int n, int len) {
   return t;
 }
 
+// The twiddles of a plan in pass order: for each pass after the first, the R -
+// 1 factors exp(-2 pi i r jm / (Ns R)) of every jm < Ns, adjacent.  Fewer than n
+// entries; padded to n.
+template <typename T>
+std::vector<cpx<T>> plan_twiddles(const FftPlan& p) {
+  std::vector<cpx<T>> t(std::max(p.n, 1), cpx<T>{1, 0});
+  for (int i = 1; i < p.npass; ++i) {
+    const FftPass& s = p.ps[i];
+    for (int jm = 0; jm < s.Ns; ++jm)
+      for (int r = 1; r < s.R; ++r) {
+        // the angle of the natural-order table: index r jm n / (Ns R) of n
+        const long k = (long)r * jm * (p.n / (s.Ns * s.R));
+        const double a = -2.0 * kPi * (double)k / (double)p.n;
+        t[s.off + jm * (s.R - 1) + r - 1] = {(T)std::cos(a), (T)std::sin(a)};
+      }
+  }
+  return t;
+}
+
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
@@ -160,7 +224,7 @@ struct Group {
   double B[3] = {0, 0, 0};
   size_t off = 0;  // element offset of this group in caller arrays
   // device buffers (regions of the context's arena)
-  Buf tw_x, wpost, tw_y, tw_z, Nt, S, ms, ms2, m7, k[7], Trep, seeds, partial, E;
+  Buf tw_x, wpost, tw_y, tw_z, ptw_x, ptw_y, ptw_z, Nt, S, ms, ms2, m7, k[7], Trep, seeds, partial, E;
   Buf tgen, tstart, tflag, S_init;  // retire/refill trials
   Buf Jrep;  // spin-transfer current density per replica (A/m^2)
   mmx_material_ext ext{};  // bulk DMI, cubic anisotropy, RKKY
@@ -174,7 +238,7 @@ struct Group {
   std::vector<double> cMs, calpha, cKu, cD;
   Buf cell[7];
   int cells_on = 0;
-  std::vector<std::vector<unsigned char>> tables;  // host twiddle tables (tw_x, wpost, tw_y, tw_z)
+  std::vector<std::vector<unsigned char>> tables;  // host twiddle tables (tw_x, wpost, tw_y, tw_z, ptw_x, ptw_y, ptw_z)
   double stt_p[3] = {0, 0, 1}, stt_P = 0, stt_lambda = 1, stt_eps2 = 0;
   int nblk = 1;       // k_fields workgroups per replica
   int nblk_last = 1;  // workgroups per replica of the last field-kernel launch
@@ -499,6 +563,9 @@ mmx_status setup_group(mmx_ctx* ctx, Group& G) {
   keep(twiddles<T>(G.xone ? 1 : G.Px, G.hx + 1));
   keep(twiddles<T>(G.Py, G.Py));
   keep(twiddles<T>(G.Pz, G.Pz));
+  keep(plan_twiddles<T>(G.plan_x));
+  keep(plan_twiddles<T>(G.plan_yf));
+  keep(plan_twiddles<T>(G.plan_zf));
   return MMX_OK;
 }
 
@@ -524,6 +591,9 @@ void arena_walk(mmx_ctx* ctx, F&& take) {
     take(G.wpost, (size_t)(G.hx + 1) * c);
     take(G.tw_y, (size_t)G.Py * c);
     take(G.tw_z, (size_t)G.Pz * c);
+    take(G.ptw_x, (size_t)G.hx * c);
+    take(G.ptw_y, (size_t)G.Py * c);
+    take(G.ptw_z, (size_t)G.Pz * c);
     take(G.Nt, (size_t)kTensorStride * G.Tz * G.Ty * G.Kx * w);
     take(G.S, (size_t)G.R * 3 * G.nz * G.Sy * G.Kx * c);
     take(G.ms, st);
@@ -593,8 +663,8 @@ mmx_status arena_init(mmx_ctx* ctx) {
   arena_assign(ctx, ctx->arena);
   for (auto& gp : ctx->groups) {
     Group& G = *gp;
-    Buf* dst[4] = {&G.tw_x, &G.wpost, &G.tw_y, &G.tw_z};
-    for (int i = 0; i < 4; ++i)
+    Buf* dst[7] = {&G.tw_x, &G.wpost, &G.tw_y, &G.tw_z, &G.ptw_x, &G.ptw_y, &G.ptw_z};
+    for (int i = 0; i < 7; ++i)
       HIP_TRY(hipMemcpy(dst[i]->p, G.tables[i].data(), G.tables[i].size(), hipMemcpyHostToDevice));
   }
   return MMX_OK;
@@ -628,7 +698,7 @@ mmx_status build_demag_group(mmx_ctx* ctx, Group& G) {
     if (n == 1) return MMX_OK;
     FftPlan p;
     make_plan(n, false, p);
-    auto tw = twiddles<double>(n, n);
+    auto tw = plan_twiddles<double>(p);
     DevBuf tb;
     HIP_TRY(tb.alloc(n * sizeof(cpx<double>)));
     HIP_TRY(hipMemcpy(tb.p, tw.data(), n * sizeof(cpx<double>), hipMemcpyHostToDevice));
@@ -698,6 +768,21 @@ bool cubic_axes(const mmx_material_ext& e, double c1[3], double c2[3], double c3
   c3[1] = c1[2] * c2[0] - c1[0] * c2[2];
   c3[2] = c1[0] * c2[1] - c1[1] * c2[0];
   return true;
+}
+
+// block relabelling of a launch (see xcd_block)
+GridMap grid_map(dim3 g) {
+  GridMap m{};
+  m.gx = g.x;
+  m.gxy = g.x * g.y;
+  const unsigned long long n = (unsigned long long)m.gxy * g.z;
+  m.per = (unsigned)(n / 8);
+  // the magic quotients are exact while index x divisor stays below 2^31
+  if (n * m.gxy < (1ull << 31)) {
+    m.mgx = magic_of((int)m.gx);
+    m.mgxy = magic_of((int)m.gxy);
+  }
+  return m;
 }
 
 template <typename T>
@@ -777,6 +862,11 @@ FArgs<T> field_args(const mmx_ctx* ctx, const Group& G, uint32_t terms) {
   a.S = G.S.as<cpx<T>>();
   a.plan = G.plan_xi;  // inverse transform: full input
   a.tw = G.tw_x.as<cpx<T>>();
+  a.ptw = G.ptw_x.as<cpx<T>>();
+  a.mhx = magic_of(G.hx);
+  a.mL = magic_of(G.L);
+  a.mnx = magic_of(G.nx);
+  a.mKx = magic_of(G.Kx);
   a.wpost = G.wpost.as<cpx<T>>();
   if ((t & T_STT) && G.jrep_on && G.stt_P != 0) {
     const double d = G.g.cell[2] * G.nz;  // free-layer thickness
@@ -856,6 +946,21 @@ bool launch_rows_reg(mmx_ctx* ctx, Group& G, FArgs<T>& a, int mode) {
   }
 }
 
+// The compile-time half-length of the LDS row kernels for group G: 32, 64, 128
+// or 256 points, the powers of two of the common film sizes, whose lines are
+// padded against bank conflicts and indexed by constants (0: the run-time
+// kernels, for every other length and where the padded lines exceed the 64 KB
+// that any tile may use).  lds(ld): bytes with ld slots per line.
+template <typename T, typename F>
+int fixed_hx(const Group& G, F&& lds) {
+  if (G.xone) return 0;
+  switch (G.hx) {
+    case 32: case 64: case 128: case 256:
+      return lds(G.hx + G.hx / 16) + kBlock * sizeof(double) <= 64 * 1024 ? G.hx : 0;
+    default: return 0;
+  }
+}
+
 template <typename T>
 mmx_status launch_fields(mmx_ctx* ctx, Group& G, FArgs<T>& a, int mode) {
   static const char* kname_reg[] = {"", "", "k_fields_heun1", "k_fields_heun2"};
@@ -869,21 +974,71 @@ mmx_status launch_fields(mmx_ctx* ctx, Group& G, FArgs<T>& a, int mode) {
   }
   G.nblk_last = G.nblk;
   dim3 grid((G.ny + G.L - 1) / G.L, G.nz, G.R);
-  const size_t lds = (a.terms & T_DEMAG) ? (2 * (size_t)3 * G.L * G.hx + G.hx) * cpxb<T>() : 0;
+  // two line buffers, the pass twiddles and, for a forward transform, the split factors
+  const bool fft = (a.terms & T_DEMAG) != 0;
+  auto lds_of = [&](int ld) {
+    return fft ? (2 * (size_t)3 * G.L * ld + G.hx + (a.fwd ? G.hx + 1 : 0)) * cpxb<T>() : size_t(0);
+  };
   hipStream_t s = ctx->stream;
   static const char* kname[] = {"k_fields_field", "k_fields_torque", "k_fields_heun1",
                                  "k_fields_heun2", "k_fields_rkk", "k_fields_rk7",
                                  "k_fields_energy"};
   ProfScope ps(ctx->prof, kname[mode], s);
-  switch (mode) {
-    case FM_FIELD: k_fields<T, FM_FIELD><<<grid, kBlock, lds, s>>>(a); break;
-    case FM_TORQUE: k_fields<T, FM_TORQUE><<<grid, kBlock, lds, s>>>(a); break;
-    case FM_HEUN1: k_fields<T, FM_HEUN1><<<grid, kBlock, lds, s>>>(a); break;
-    case FM_HEUN2: k_fields<T, FM_HEUN2><<<grid, kBlock, lds, s>>>(a); break;
-    case FM_RKK: k_fields<T, FM_RKK><<<grid, kBlock, lds, s>>>(a); break;
-    case FM_RK7: k_fields<T, FM_RK7><<<grid, kBlock, lds, s>>>(a); break;
-    default: k_fields<T, FM_ENERGY><<<grid, kBlock, lds, s>>>(a); break;
+  a.map = grid_map(grid);
+  const bool ext = (a.terms & (T_DMI_BULK | T_CUBIC | T_RKKY)) || a.kbb != 0 || a.Acell ||
+                   G.cells_on;
+  // the integrator stages have variants of fixed length; where the register
+  // row kernels take the Heun stages (FP32), only the RK stages need them
+  constexpr bool kHeunFixed = !std::is_same<T, float>::value;
+  const int hxf = (fft && !ext) ? fixed_hx<T>(G, lds_of) : 0;
+  const size_t lds = lds_of(hxf ? hxf + hxf / 16 : G.hx);
+#define MMX_FIELDS(M)                                        \
+  case M:                                                    \
+    if (ext)                                                 \
+      k_fields<T, M, true, 0><<<grid, kBlock, lds, s>>>(a);    \
+    else                                                     \
+      k_fields<T, M, false, 0><<<grid, kBlock, lds_of(G.hx), s>>>(a); \
+    break;
+#define MMX_FIELDS_HX(M)                                                             \
+  case M:                                                                            \
+    switch (hxf) {                                                                   \
+      case 32: k_fields<T, M, false, 32><<<grid, kBlock, lds, s>>>(a); break;        \
+      case 64: k_fields<T, M, false, 64><<<grid, kBlock, lds, s>>>(a); break;        \
+      case 128: k_fields<T, M, false, 128><<<grid, kBlock, lds, s>>>(a); break;      \
+      case 256: k_fields<T, M, false, 256><<<grid, kBlock, lds, s>>>(a); break;      \
+      default:                                                                       \
+        if (ext)                                                                     \
+          k_fields<T, M, true, 0><<<grid, kBlock, lds, s>>>(a);                      \
+        else                                                                         \
+          k_fields<T, M, false, 0><<<grid, kBlock, lds, s>>>(a);                     \
+        break;                                                                       \
+    }                                                                                \
+    break;
+  if constexpr (kHeunFixed) {
+    switch (mode) {
+      MMX_FIELDS_HX(FM_FIELD)
+      MMX_FIELDS(FM_TORQUE)
+      MMX_FIELDS_HX(FM_HEUN1)
+      MMX_FIELDS_HX(FM_HEUN2)
+      MMX_FIELDS_HX(FM_RKK)
+      MMX_FIELDS_HX(FM_RK7)
+      MMX_FIELDS(FM_ENERGY)
+      default: return fail(MMX_EINVAL, "field kernel mode");
+    }
+  } else {
+    switch (mode) {
+      MMX_FIELDS_HX(FM_FIELD)
+      MMX_FIELDS(FM_TORQUE)
+      MMX_FIELDS(FM_HEUN1)
+      MMX_FIELDS(FM_HEUN2)
+      MMX_FIELDS_HX(FM_RKK)
+      MMX_FIELDS_HX(FM_RK7)
+      MMX_FIELDS(FM_ENERGY)
+      default: return fail(MMX_EINVAL, "field kernel mode");
+    }
   }
+#undef MMX_FIELDS_HX
+#undef MMX_FIELDS
   HIP_TRY(hipGetLastError());
   return MMX_OK;
 }
@@ -934,16 +1089,41 @@ mmx_status launch_xfwd(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb
   x.msr = (G.cells_on && !G.cMs.empty()) ? G.cell[0].as<T>() : nullptr;
   x.do_fft = demag ? 1 : 0;
   x.S = G.S.as<cpx<T>>();
-  x.tw = G.tw_x.as<cpx<T>>();
+  x.tw = G.ptw_x.as<cpx<T>>();
   x.wpost = G.wpost.as<cpx<T>>();
   x.plan = G.plan_x;
   x.nx = G.nx; x.ny = G.ny; x.nz = G.nz; x.N = G.N; x.Sy = G.Sy; x.Kx = G.Kx; x.hx = G.hx;
   x.L = G.L; x.xone = G.xone;
+  // a pruned transform never reads k >= hx/2 = npair: those slots stay unfilled
+  x.kw = (demag && !G.plan_x.prune) ? G.hx : (G.xone ? 1 : (G.nx + 1) / 2);
+  x.mkw = magic_of(x.kw);
+  x.mL = magic_of(G.L);
+  x.mKx = magic_of(G.Kx);
   x.done = done;
   dim3 grid((G.ny + G.L - 1) / G.L, G.nz, G.R);
-  const size_t lds = demag ? (2 * (size_t)3 * G.L * G.hx + 2 * G.hx + 1) * cpxb<T>() : 0;
+  auto lds_of = [&](int ld) {
+    return demag ? (2 * (size_t)3 * G.L * ld + 2 * G.hx + 1) * cpxb<T>() : size_t(0);
+  };
+  x.map = grid_map(grid);
   ProfScope ps(ctx->prof, demag ? "k_xfwd" : "k_combine", s);
-  k_xfwd<T><<<grid, kBlock, lds, s>>>(x);
+  auto go = [&](auto k0, auto k1, auto k6, int ld) {
+    if (cb.ncoef == 0)
+      k0<<<grid, kBlock, lds_of(ld), s>>>(x);
+    else if (cb.ncoef == 1)
+      k1<<<grid, kBlock, lds_of(ld), s>>>(x);
+    else
+      k6<<<grid, kBlock, lds_of(ld), s>>>(x);
+  };
+#define MMX_XFWD(HX) \
+  go(k_xfwd<T, 0, HX>, k_xfwd<T, 1, HX>, k_xfwd<T, 6, HX>, HX ? Line<HX>::LD : G.hx)
+  switch (fixed_hx<T>(G, lds_of)) {
+    case 32: MMX_XFWD(32); break;
+    case 64: MMX_XFWD(64); break;
+    case 128: MMX_XFWD(128); break;
+    case 256: MMX_XFWD(256); break;
+    default: MMX_XFWD(0); break;
+  }
+#undef MMX_XFWD
   HIP_TRY(hipGetLastError());
   return MMX_OK;
 }
@@ -1063,9 +1243,13 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
     y.Nt = G.Nt.as<T>();
     y.ny = G.ny; y.Py = G.Py; y.Kx = G.Kx; y.Ty = G.Ty; y.Sy = G.Sy; y.nz = G.nz; y.Pz = G.Pz;
     y.Tz = G.Tz;
+    y.ptw = G.ptw_y.as<cpx<T>>();
+    y.mny = magic_of(G.ny);
+    y.mnz = magic_of(G.nz);
     y.done = done;
     if (!G.is3d) {
       y.W = G.Wy;
+      y.mW = magic_of(G.Wy);
       y.tw = G.tw_y.as<cpx<T>>();
       y.pf = G.plan_yf;
       y.pi = G.plan_yi;
@@ -1082,17 +1266,34 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
       if (!launch_yconv_reg<T>(G, y, s)) {
         if (sw) return fail(MMX_ESTATE, "switching check folded into a column kernel without it");
         dim3 grid((G.Kx + G.Wy - 1) / G.Wy, 1, G.R);
-        k_yconv<T><<<grid, kBlock, (2 * (size_t)3 * G.Wy * G.Py + G.Py) * cpxb<T>(), s>>>(y);
+        y.map = grid_map(grid);
+        // fixed-length variants as for the rows (fixed_hx); FP32 columns of 64
+        // to 256 points have the register kernel
+        auto lds_of = [&](int ld) { return (2 * (size_t)3 * G.Wy * ld + G.Py) * cpxb<T>(); };
+        const bool fits = lds_of(G.Py + G.Py / 16) <= 64 * 1024;
+        constexpr bool f64 = std::is_same<T, double>::value;
+        if (f64 && G.Py == 64 && fits)
+          k_yconv<T, f64 ? 64 : 0><<<grid, kBlock, lds_of(Line<64>::LD), s>>>(y);
+        else if (f64 && G.Py == 128 && fits)
+          k_yconv<T, f64 ? 128 : 0><<<grid, kBlock, lds_of(Line<128>::LD), s>>>(y);
+        else if (f64 && G.Py == 256 && fits)
+          k_yconv<T, f64 ? 256 : 0><<<grid, kBlock, lds_of(Line<256>::LD), s>>>(y);
+        else if (G.Py == 512 && fits)
+          k_yconv<T, 512><<<grid, kBlock, lds_of(Line<512>::LD), s>>>(y);
+        else
+          k_yconv<T, 0><<<grid, kBlock, lds_of(G.Py), s>>>(y);
       }
       HIP_TRY(hipGetLastError());
     } else if (yz_applies<T>(G) && !(G.yz_split && ypass_reg_applies<T>(G))) {
       y.W = G.Wz;
+      y.mW = magic_of(G.Wz);
       y.tw = G.tw_y.as<cpx<T>>();
       y.twz = G.tw_z.as<cpx<T>>();
       y.pf = G.plan_yf;
       y.pi = G.plan_yi;
       dim3 g((G.Kx + G.Wz - 1) / G.Wz, 1, G.R);
       const size_t lds = lds_yz<T>(G, G.Wz);
+      y.map = grid_map(g);
       ProfScope ps(ctx->prof, "k_yzconv", s);
       if (G.nz <= 2)
         k_yzconv<T, 2><<<g, kBlock, lds, s>>>(y);
@@ -1103,11 +1304,13 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
       HIP_TRY(hipGetLastError());
     } else {
       y.W = G.Wy;
+      y.mW = magic_of(G.Wy);
       y.tw = G.tw_y.as<cpx<T>>();
       y.pf = G.plan_yf;
       y.pi = G.plan_yi;
       dim3 gy((G.Kx + G.Wy - 1) / G.Wy, 3 * G.nz, G.R);
       const size_t ldy = lds_ycols<T>(true, G.Wy, G.Py);
+      y.map = grid_map(gy);
       {
         ProfScope ps(ctx->prof, "k_ypass_fwd", s);
         if (!launch_ypass_reg<T>(G, y, false, s)) k_ypass<T, false><<<gy, kBlock, ldy, s>>>(y);
@@ -1115,6 +1318,8 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
       HIP_TRY(hipGetLastError());
       YArgs<T> zz = y;
       zz.W = G.Wz;
+      zz.mW = magic_of(G.Wz);
+      zz.ptw = G.ptw_z.as<cpx<T>>();
       zz.tw = G.tw_z.as<cpx<T>>();
       zz.twz = G.tw_z.as<cpx<T>>();
       zz.pf = G.plan_zf;
@@ -1131,6 +1336,7 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
             k_zconv_reg<T, 8><<<gz, kBlock, 0, s>>>(zz);
         } else if (!launch_zline_reg<T>(G, zz, s)) {
           dim3 gz((G.Kx + G.Wz - 1) / G.Wz, G.Py, G.R);
+          zz.map = grid_map(gz);
           k_zconv<T><<<gz, kBlock, (2 * (size_t)3 * G.Wz * G.Pz + G.Pz) * cpxb<T>(), s>>>(zz);
         }
       }
@@ -1494,9 +1700,9 @@ mmx_status heun_fused(mmx_ctx* ctx, Group& G, const FusedTiles& ft, T* mg, doubl
   a.pxi = G.plan_xi;
   a.pyf = G.plan_yf;
   a.pyi = G.plan_yi;
-  a.tw_x = G.tw_x.as<cpx<T>>();
+  a.tw_x = G.ptw_x.as<cpx<T>>();
   a.wpost = G.wpost.as<cpx<T>>();
-  a.tw_y = G.tw_y.as<cpx<T>>();
+  a.tw_y = G.ptw_y.as<cpx<T>>();
   a.Nt = G.Nt.as<T>();
   a.Ty = G.Ty;
   a.Py = G.Py;
@@ -2127,17 +2333,21 @@ mmx_status time_eval(mmx_ctx* ctx, Group& G, float& ms) {
   ep.out = G.k[0].p;
   mmx_status st = MMX_OK;
   float best = 1e30f;
-  // five repetitions, the fastest of the last four (the first warms caches):
-  // single evaluations of small grids take tens of microseconds
-  for (int rep = 0; rep < 5 && st == MMX_OK; ++rep) {
+  // two repetitions of a few evaluations, the first to warm caches: one
+  // evaluation of a small grid takes 20 us, as long as its launches take the
+  // host, and the spread of single ones hid differences of a third between
+  // tiles
+  const int evals = (size_t)G.R * G.N <= (1u << 19) ? 5 : 2;
+  for (int rep = 0; rep < 2 && st == MMX_OK; ++rep) {
     (void)hipEventRecord(a, ctx->stream);
-    st = eval_group<T>(ctx, G, G.ms.as<T>(), Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
-                       ctx->terms & ~MMX_THERMAL);
+    for (int i = 0; i < evals && st == MMX_OK; ++i)
+      st = eval_group<T>(ctx, G, G.ms.as<T>(), Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
+                         ctx->terms & ~MMX_THERMAL);
     (void)hipEventRecord(b, ctx->stream);
     (void)hipEventSynchronize(b);
     float t = 0;
     (void)hipEventElapsedTime(&t, a, b);
-    if (rep > 0) best = std::min(best, t);
+    if (rep > 0) best = std::min(best, t / evals);
   }
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
@@ -2161,6 +2371,7 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
       float t;
       MMX_TRY(time_eval<T>(ctx, G, t));
       if (t < bt) { bt = t; bestL = L; }
+      if (t > 1.25f * bt) break;  // larger tiles only get slower from here
     }
     bt = 1e30f;
     for (int W : cand) {
@@ -2170,6 +2381,7 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
       float t;
       MMX_TRY(time_eval<T>(ctx, G, t));
       if (t < bt) { bt = t; bestW = W; }
+      if (t > 1.25f * bt) break;
     }
     // few-layer groups: the fused y-z kernel (its column tile tuned) against
     // the separate register y passes around the z pass
@@ -2184,6 +2396,7 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
         float t;
         MMX_TRY(time_eval<T>(ctx, G, t));
         if (t < bt) { bt = t; bestWz = W; }
+        if (t > 1.25f * bt) break;
       }
       t_fused = bt;
     }
