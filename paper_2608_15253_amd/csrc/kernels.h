@@ -134,6 +134,23 @@ __device__ inline int stop_flag(const int* done) {
 }
 __device__ inline bool stopped(int flag) { return __builtin_amdgcn_readfirstlane(flag) != 0; }
 
+// 1 / sqrt(x), the factor that normalises a state.  FP32: the hardware
+// reciprocal root (1 ulp) and one Newton step, eight instructions with an
+// error of 0.6 ulp, in place of the correctly rounded root and quotient, some
+// thirty with 1 ulp between them.  A square within one step of 1 (1.2e-7)
+// gives exactly 1, as the correctly rounded forms do: scaling by 1 - 6e-8
+// would round every component of a state that is as normal as FP32 can hold
+// (a macrospin's error after 2000 rotation steps 3.7e-7 instead of 0.8e-7).
+// Arguments far from 1 (no state has them, save one that has blown up) keep
+// the library forms and their special values.
+__device__ inline double inv_norm(double x) { return 1.0 / sqrt(x); }
+__device__ inline float inv_norm(float x) {
+  if (!(x > 1e-30f && x < 1e30f)) return 1.0f / sqrtf(x);
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float e = fmaf(-x * y, y, 1.0f);
+  return fabsf(x - 1.0f) <= 1.3e-7f ? 1.0f : fmaf(0.5f * y, e, y);
+}
+
 // The three components of a cell of one replica (component stride N).  With
 // O32 the byte offsets are formed in 32 bits (the caller guarantees
 // 3 N sizeof(T) < 2^32): with the replica's base pointer uniform across the
@@ -267,7 +284,7 @@ __global__ void __launch_bounds__(kBlock) k_xfwd(XArgs<T> a) {
         }
         if (a.normalise) {
           const T inv =
-              T(1) / sqrt(mv[h][0] * mv[h][0] + mv[h][1] * mv[h][1] + mv[h][2] * mv[h][2]);
+              inv_norm(mv[h][0] * mv[h][0] + mv[h][1] * mv[h][1] + mv[h][2] * mv[h][2]);
           mv[h][0] *= inv; mv[h][1] *= inv; mv[h][2] *= inv;
           if (a.nonfinite && !(fabs(mv[h][0]) + fabs(mv[h][1]) + fabs(mv[h][2]) <= T(3)))
             *a.nonfinite = 1;
@@ -829,6 +846,7 @@ struct FArgs {
   const double* Jrep;
   double stt_c;
   T sttp[3], stt_P, stt_L2, stt_e2;
+  T stt_eps1;         // stt_P / 2, the asymmetry factor for Lambda = 1
 };
 
 // Exchange (six-point Laplacian), interfacial DMI (central differences), both
@@ -1027,7 +1045,10 @@ template <typename T>
 __device__ inline void stt_tau(const FArgs<T>& a, T gpm, T alpha, T bJ, const T m[3], T tau[3]) {
   const T* p = a.sttp;
   const T mp = m[0] * p[0] + m[1] * p[1] + m[2] * p[2];
-  const T eps = a.stt_P * a.stt_L2 / ((a.stt_L2 + T(1)) + (a.stt_L2 - T(1)) * mp);
+  // without asymmetry (Lambda = 1) the quotient does not depend on m
+  const T eps = a.stt_L2 == T(1)
+                    ? a.stt_eps1
+                    : a.stt_P * a.stt_L2 / ((a.stt_L2 + T(1)) + (a.stt_L2 - T(1)) * mp);
   const T x[3] = {m[1] * p[2] - m[2] * p[1], m[2] * p[0] - m[0] * p[2], m[0] * p[1] - m[1] * p[0]};
   const T xx[3] = {m[1] * x[2] - m[2] * x[1], m[2] * x[0] - m[0] * x[2], m[0] * x[1] - m[1] * x[0]};
   const T c1 = gpm * bJ * (eps - alpha * a.stt_e2);
@@ -1085,28 +1106,55 @@ __device__ inline void llg_omega(const T mc[3], const T H[3], T gpm, T alpha, T 
   o[2] = gpm * (H[2] + alpha * cz);
 }
 
-// Rodrigues rotation of v about w by the angle |w|:
-// v cos|w| + (w x v) sin|w|/|w| + w (w.v) (1 - cos|w|)/|w|^2, with
-// 1 - cos|w| = 2 sin^2(|w|/2) (no cancellation) and Taylor series of both
-// ratios below |w| = 1e-3.
+// sin|w| / |w| and (1 - cos|w|) / |w|^2 from t2 = |w|^2 <= 1/4: Taylor series
+// whose first dropped term is below a tenth of the type's rounding
+__device__ inline void rot_series(float t2, float& s1, float& s2) {
+  s1 = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 1.0f / 362880, -1.0f / 5040), 1.0f / 120), -1.0f / 6),
+            1.0f);
+  s2 = fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 1.0f / 3628800, -1.0f / 40320), 1.0f / 720),
+                     -1.0f / 24), 0.5f);
+}
+__device__ inline void rot_series(double t2, double& s1, double& s2) {
+  // 1 / (2k + 1)! and 1 / (2k + 2)!, alternating, k = 8 .. 0
+  constexpr double a[9] = {1.0 / 355687428096000.0, -1.0 / 1307674368000.0, 1.0 / 6227020800.0,
+                           -1.0 / 39916800.0, 1.0 / 362880.0, -1.0 / 5040.0, 1.0 / 120.0,
+                           -1.0 / 6.0, 1.0};
+  constexpr double b[9] = {1.0 / 6402373705728000.0, -1.0 / 20922789888000.0,
+                           1.0 / 87178291200.0, -1.0 / 479001600.0, 1.0 / 3628800.0,
+                           -1.0 / 40320.0, 1.0 / 720.0, -1.0 / 24.0, 0.5};
+  s1 = a[0];
+  s2 = b[0];
+#pragma unroll
+  for (int k = 1; k < 9; ++k) {
+    s1 = fma(s1, t2, a[k]);
+    s2 = fma(s2, t2, b[k]);
+  }
+}
+
+// Rodrigues rotation of v about w by the angle |w|, as an increment:
+// v + (w x v) sin|w|/|w| + (w (w.v) - |w|^2 v) (1 - cos|w|)/|w|^2.  The increment
+// is small (a step of dt turns a cell by gamma B dt, 0.02 for 1 T and 0.1 ps),
+// and so is the rounding of its factors; written as v cos|w| + ... the
+// rounding of cos|w| near 1 moved v by as much as the final one.  The two
+// ratios come from Taylor series up to |w| = 1/2; beyond, 1 - cos|w| =
+// 2 sin^2(|w|/2) (no cancellation): the root, the quotients and the two sines
+// (half of a macrospin's step) are left to extreme steps.
 template <typename T>
 __device__ inline void rodrigues(const T v[3], const T w[3], T out[3]) {
   const T t2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
   T s1, s2;  // sin|w| / |w|, (1 - cos|w|) / |w|^2
-  if (t2 < T(1e-6)) {
-    s1 = T(1) - t2 * (T(1) / T(6) - t2 * (T(1) / T(120)));
-    s2 = T(0.5) - t2 * (T(1) / T(24) - t2 * (T(1) / T(720)));
+  if (t2 <= T(0.25)) {
+    rot_series(t2, s1, s2);
   } else {
     const T t = sqrt(t2);
     const T sh = sin(T(0.5) * t);
     s1 = sin(t) / t;
     s2 = T(2) * sh * sh / t2;
   }
-  const T c = T(1) - t2 * s2;  // cos|w|
   const T wv = w[0] * v[0] + w[1] * v[1] + w[2] * v[2];
-  out[0] = c * v[0] + s1 * (w[1] * v[2] - w[2] * v[1]) + s2 * wv * w[0];
-  out[1] = c * v[1] + s1 * (w[2] * v[0] - w[0] * v[2]) + s2 * wv * w[1];
-  out[2] = c * v[2] + s1 * (w[0] * v[1] - w[1] * v[0]) + s2 * wv * w[2];
+  out[0] = v[0] + (s1 * (w[1] * v[2] - w[2] * v[1]) + s2 * (wv * w[0] - t2 * v[0]));
+  out[1] = v[1] + (s1 * (w[2] * v[0] - w[0] * v[2]) + s2 * (wv * w[1] - t2 * v[1]));
+  out[2] = v[2] + (s1 * (w[0] * v[1] - w[1] * v[0]) + s2 * (wv * w[2] - t2 * v[2]));
 }
 
 // o += m x t
@@ -1167,7 +1215,7 @@ __device__ inline void heun_correct(T gpm, T alpha, bool rot, const T mc[3], con
     for (int c = 0; c < 3; ++c) w[c] = T(0.5) * dt * (k1v[c] + o[c]);
     rodrigues(mo, w, mn);
     if constexpr (sizeof(T) == sizeof(float)) {
-      const T inv = T(1) / sqrt(mn[0] * mn[0] + mn[1] * mn[1] + mn[2] * mn[2]);
+      const T inv = inv_norm(mn[0] * mn[0] + mn[1] * mn[1] + mn[2] * mn[2]);
 #pragma unroll
       for (int c = 0; c < 3; ++c) mn[c] *= inv;
     }
@@ -1175,7 +1223,7 @@ __device__ inline void heun_correct(T gpm, T alpha, bool rot, const T mc[3], con
     T u[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) u[c] = T(0.5) * (mo[c] + mc[c]) + T(0.5) * dt * k[c];
-    const T inv = T(1) / sqrt(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+    const T inv = inv_norm(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) mn[c] = u[c] * inv;
   }
@@ -1402,7 +1450,7 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
           mv[c] = sv;
         }
         if (a.cnext == 2) {
-          const T inv = T(1) / sqrt(mv[0] * mv[0] + mv[1] * mv[1] + mv[2] * mv[2]);
+          const T inv = inv_norm(mv[0] * mv[0] + mv[1] * mv[1] + mv[2] * mv[2]);
           mv[0] *= inv; mv[1] *= inv; mv[2] *= inv;
         }
         const T ws = (EXT && a.msr) ? a.msr[cell] : T(1);  // transform input M = Ms_i m

@@ -876,6 +876,7 @@ FArgs<T> field_args(const mmx_ctx* ctx, const Group& G, uint32_t terms) {
     a.stt_P = (T)G.stt_P;
     a.stt_L2 = (T)(G.stt_lambda * G.stt_lambda);
     a.stt_e2 = (T)G.stt_eps2;
+    a.stt_eps1 = a.stt_P / T(2);
   } else {
     a.terms &= ~(unsigned)T_STT;
   }
@@ -1758,16 +1759,29 @@ mmx_status heun_macrospin(mmx_ctx* ctx, Group& G, T* mg, double dt, int64_t n_st
   FArgs<T> a = field_args<T>(ctx, G, ctx->terms);
   a.dth = dt;
   a.dt_th = dt;
-  const dim3 grid((unsigned)((G.R + 255) / 256));
+  // lanes per replica: the most that leave at most two waves per SIMD (2048
+  // waves share the issue slots of 1024 SIMDs at no cost to each other)
+  const bool ext = (a.terms & (T_DMI_BULK | T_CUBIC | T_RKKY)) != 0;
+  const bool refill = mr.tgen != nullptr;
+  const int most = (int)std::min<long long>(16, 2048LL * 64 / G.R);
+  const int lanes = refill || !(ctx->terms & MMX_THERMAL) ? 1
+                    : most >= 16 ? 16 : most >= 8 ? 8 : most >= 4 ? 4 : 1;
+  const dim3 grid((unsigned)(((long long)G.R * lanes + 63) / 64));
   for (int64_t done = 0; done < n_steps;) {
     const int n = (int)std::min<int64_t>(n_steps - done, 8192);
     ProfScope ps(ctx->prof, "k_macrospin", ctx->stream);
+    const uint64_t at = step0 + (uint64_t)done;
+    auto go = [&](auto kern) { kern<<<grid, 64, 0, ctx->stream>>>(a, mg, dt, n, at, tsw, G.R, mr); };
+#define MMX_MACRO(ROT, EXT)                            \
+  (lanes == 16  ? go(k_macrospin<T, ROT, EXT, 16>)     \
+   : lanes == 8 ? go(k_macrospin<T, ROT, EXT, 8>)      \
+   : lanes == 4 ? go(k_macrospin<T, ROT, EXT, 4>)      \
+                : go(k_macrospin<T, ROT, EXT, 1>))
     if (rot)
-      k_macrospin<T, true><<<grid, 256, 0, ctx->stream>>>(a, mg, dt, n, step0 + (uint64_t)done,
-                                                          tsw, G.R, mr);
+      ext ? MMX_MACRO(true, true) : MMX_MACRO(true, false);
     else
-      k_macrospin<T, false><<<grid, 256, 0, ctx->stream>>>(a, mg, dt, n, step0 + (uint64_t)done,
-                                                           tsw, G.R, mr);
+      ext ? MMX_MACRO(false, true) : MMX_MACRO(false, false);
+#undef MMX_MACRO
     HIP_TRY(hipGetLastError());
     done += n;
   }
