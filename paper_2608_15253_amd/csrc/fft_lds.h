@@ -233,7 +233,7 @@ struct Dft {
 // are zero and not read.
 template <typename T, bool INV, int R, bool FIRST, bool HALF>
 __device__ inline void stockham_pass(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
-                                     const FftPass& p, int nlines, const cpx<T>* __restrict__ tw,
+                                     const FftPass p, int nlines, const cpx<T>* __restrict__ tw,
                                      int tid, int nthr, int ld) {
   static_assert(!HALF || (FIRST && R % 2 == 0), "pruned first pass");
   const int nb = p.nb, Ns = p.Ns;
@@ -273,16 +273,21 @@ __device__ inline void stockham_pass(const cpx<T>* __restrict__ src, cpx<T>* __r
 // result.  `tw` is the plan's pass-ordered table (plan_twiddles).  Lines start
 // every `ld` slots (0: every n, contiguous).  Must be called by the whole
 // workgroup; ends with a barrier.
-template <typename T, bool INV>
-__device__ cpx<T>* lds_fft(cpx<T>* a, cpx<T>* b, int nlines, const FftPlan& p,
+//
+// NT: threads of the workgroup.  Each pass's constants are read while the one
+// before it runs (a first touch of an argument line takes 70 ns).
+template <typename T, bool INV, int NT = 256>
+__device__ inline cpx<T>* lds_fft(cpx<T>* a, cpx<T>* b, int nlines, const FftPlan& p,
                            const cpx<T>* __restrict__ tw, int ld = 0) {
   if (p.npass == 0) return a;
   if (ld == 0) ld = p.n;
-  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int tid = threadIdx.x;
+  constexpr int nthr = NT;
+  FftPass ps = p.ps[0];
 #define MMX_PASS(R, FIRST, HALF) \
   stockham_pass<T, INV, R, FIRST, HALF>(a, b, ps, nlines, tw, tid, nthr, ld)
+  FftPass nx = p.ps[1];
   {
-    const FftPass& ps = p.ps[0];
     if (!INV && p.prune) {
       switch (ps.R) {
         case 2: MMX_PASS(2, true, !INV); break;
@@ -306,7 +311,8 @@ __device__ cpx<T>* lds_fft(cpx<T>* a, cpx<T>* b, int nlines, const FftPlan& p,
   }
   __syncthreads();
   for (int i = 1; i < p.npass; ++i) {
-    const FftPass& ps = p.ps[i];
+    ps = nx;
+    nx = p.ps[min(i + 1, kMaxPass - 1)];
     cpx<T>* t = a;
     a = b;
     b = t;

@@ -78,7 +78,7 @@ __device__ inline void fused_forward(const HeunFusedArgs<T>& a, const T* __restr
       for (int c = 0; c < 3; ++c) A[(c * C + l) * hx + k] = v[c];
     }
     __syncthreads();
-    const cpx<T>* Z = lds_fft<T, false>(A, Bf, 3 * C, a.pxf, twx);
+    const cpx<T>* Z = lds_fft<T, false, kFusedBlock>(A, Bf, 3 * C, a.pxf, twx);
     for (int t = threadIdx.x; t < 3 * C * Kx; t += blockDim.x) {
       const int line = t / Kx, kx = t - line * Kx;
       const int c = udiv(line, C), l = line - c * C, y = y0 + l;
@@ -104,7 +104,7 @@ __device__ inline void fused_forward(const HeunFusedArgs<T>& a, const T* __restr
       A[(c * W + w) * Py + y] = v;
     }
     __syncthreads();
-    cpx<T>* Y = lds_fft<T, false>(A, Bf, 3 * W, a.pyf, twy);
+    cpx<T>* Y = lds_fft<T, false, kFusedBlock>(A, Bf, 3 * W, a.pyf, twy);
     cpx<T>* scratch = (Y == A) ? Bf : A;
     for (int t = threadIdx.x; t < W * Py; t += blockDim.x) {
       const int w = umod(t, W), ky = udiv(t, W), kx = kx0 + w;
@@ -116,7 +116,7 @@ __device__ inline void fused_forward(const HeunFusedArgs<T>& a, const T* __restr
                    Y[(1 * W + w) * Py + ky], Y[(2 * W + w) * Py + ky]);
     }
     __syncthreads();
-    const cpx<T>* Yi = lds_fft<T, true>(Y, scratch, 3 * W, a.pyi, twy);
+    const cpx<T>* Yi = lds_fft<T, true, kFusedBlock>(Y, scratch, 3 * W, a.pyi, twy);
     for (int t = threadIdx.x; t < 3 * W * ny; t += blockDim.x) {
       const int w = umod(t, W), rest = udiv(t, W), y = umod(rest, ny), c = udiv(rest, ny);
       if (kx0 + w < Kx) X[((size_t)c * ny + y) * Kx + kx0 + w] = Yi[(c * W + w) * Py + y];
@@ -151,7 +151,7 @@ __device__ inline const T* fused_inverse_chunk(const HeunFusedArgs<T>& a, int q,
     A[line * hx + k] = Zv;
   }
   __syncthreads();
-  return reinterpret_cast<const T*>(lds_fft<T, true>(A, Bf, 3 * C, a.pxi, twx));
+  return reinterpret_cast<const T*>(lds_fft<T, true, kFusedBlock>(A, Bf, 3 * C, a.pxi, twx));
 }
 
 template <typename T>

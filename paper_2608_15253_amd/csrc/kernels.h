@@ -125,6 +125,24 @@ __device__ inline auto table_mover(cpx<T>* dst, const cpx<T>* __restrict__ src, 
       n, [src](int t) { return src[(unsigned)t]; }, [dst](int t, cpx<T> w) { dst[t] = w; });
 }
 
+// Reads one word of every 64-byte line of the kernel's arguments at once: read
+// where they are first used, one line after the other, each costs 70 ns (260 ns
+// for a plain launch, whose arguments are in host memory).
+template <typename A>
+__device__ inline void touch_args(const A& a) {
+  const int* w = reinterpret_cast<const int*>(&a);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(A) / 4); i += 16) asm volatile("" ::"s"(w[i]));
+}
+
+// A uniform argument kept in its register: the compiler would rather read it
+// again, and wait for it, in every block that uses it.
+template <typename V>
+__device__ inline V pinned(V v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 // The integrator's stop flag (set once t_end is reached), loaded through a
 // vector register: unlike a scalar load, whose wait also covers every later
 // argument load, it stays in flight while the kernel starts its other loads.
@@ -234,6 +252,7 @@ struct XArgs {
 // half-length if known at compile time, else 0
 template <typename T, int NC, int HX>
 __global__ void __launch_bounds__(kBlock) k_xfwd(XArgs<T> a) {
+  touch_args(a);
   const int dn = stop_flag(a.done);
   extern __shared__ unsigned char smem_raw[];
   cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -381,11 +400,13 @@ __device__ inline void switch_check(const double* part, double* tsw, int nblk, i
 // PY: the padded y length if known at compile time, else 0
 template <typename T, int PY>
 __global__ void __launch_bounds__(kBlock) k_yconv(YArgs<T> a) {
+  touch_args(a);
   const int dn = stop_flag(a.done);
   extern __shared__ unsigned char smem_raw[];
   cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
   const int W = a.W, Py = PY ? PY : a.Py, ld = PY ? Line<PY>::LD : Py;
   const int ny = a.ny, Kx = a.Kx, nl = 3 * W;
+  const unsigned mW = pinned(a.mW), mny = pinned(a.mny);
   cpx<T>* Bf = A + nl * ld;
   cpx<T>* tw = Bf + nl * ld;
   // neighbouring column tiles share the cache lines of the spectrum rows:
@@ -398,9 +419,9 @@ __global__ void __launch_bounds__(kBlock) k_yconv(YArgs<T> a) {
   // rows y < ny only: the others are zero, and the pruned transform does not
   // read them.  t runs over columns, rows, components (columns fastest)
   auto place = [&](int t, int& w, int& c, int& y) {
-    const int u = mdiv(t, a.mW);
+    const int u = mdiv(t, mW);
     w = t - u * W;
-    c = mdiv(u, a.mny);
+    c = mdiv(u, mny);
     y = u - c * ny;
   };
   // columns past the last read a live one and are not stored; offsets are
@@ -430,7 +451,7 @@ __global__ void __launch_bounds__(kBlock) k_yconv(YArgs<T> a) {
   const int ntens = W * Py;
   T pre[kPre][4];
   auto tens = [&](int t, int& w, int& ky, T& sy) -> const T* {
-    ky = mdiv(t, a.mW);
+    ky = mdiv(t, mW);
     w = t - ky * W;
     const bool lo = 2 * ky <= Py;
     sy = lo ? T(1) : T(-1);
@@ -487,6 +508,7 @@ __global__ void __launch_bounds__(kBlock) k_yconv(YArgs<T> a) {
 // ---------------------------------------------------------------------------
 template <typename T, bool INV>
 __global__ void __launch_bounds__(kBlock) k_ypass(YArgs<T> a) {
+  touch_args(a);
   const int dn = stop_flag(a.done);
   extern __shared__ unsigned char smem_raw[];
   cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -533,6 +555,7 @@ __global__ void __launch_bounds__(kBlock) k_ypass(YArgs<T> a) {
 // 3-D: z transform + full tensor product + inverse z transform, per ky.
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_zconv(YArgs<T> a) {
+  touch_args(a);
   const int dn = stop_flag(a.done);
   extern __shared__ unsigned char smem_raw[];
   cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -703,6 +726,7 @@ __global__ void __launch_bounds__(kBlock) k_zconv_reg(YArgs<T> a) {
 // the Py padded rows.
 template <typename T, int NZ>
 __global__ void __launch_bounds__(kBlock) k_yzconv(YArgs<T> a) {
+  touch_args(a);
   const int dn = stop_flag(a.done);
   extern __shared__ unsigned char smem_raw[];
   cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -833,6 +857,7 @@ struct FArgs {
   T cn[6];
   int cnext, cstage;
   T* mnext;
+  int* nfnext;        // set to 1 if a normalised next state is not finite (null: no check)
   FftPlan plan_f;     // forward x plan (pruned like the one of k_xfwd)
   T* hd_out;          // if set: the exact demag field is also stored here
   int rot;            // Heun epilogues take the rotation (Depondt-Mertens) update
@@ -1256,6 +1281,7 @@ __device__ inline uint64_t noise_step(const FArgs<T>& a, int r, uint64_t step_no
 // HX: the x half-length if known at compile time, else 0.
 template <typename T, int MODE, bool EXT, int HX>
 __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
+  touch_args(a);
   const int dn = (MODE != FM_ENERGY) ? stop_flag(a.done) : 0;
   extern __shared__ unsigned char smem_raw[];
   cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -1280,17 +1306,19 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
     struct Pair {
       cpx<T> k, c, w;
     };
+    const unsigned mhx = pinned(a.mhx), mL = pinned(a.mL);
+    const int xone = pinned(a.xone);
     auto rows = mover<Pair, 3>(
         nl * hx,
         [&](int t) {
-          const int line = HX ? t / hx : mdiv(t, a.mhx), k = t - line * hx;
-          const int c = mdiv(line, a.mL), l = line - c * L;
+          const int line = HX ? t / hx : mdiv(t, mhx), k = t - line * hx;
+          const int c = mdiv(line, mL), l = line - c * L;
           const cpx<T>* row = Sr + (size_t)c * cs + (unsigned)(min(l, live - 1) * Kx);
-          return Pair{row[k], row[a.xone ? 0 : hx - k], a.wpost[(unsigned)k]};
+          return Pair{row[k], row[xone ? 0 : hx - k], a.wpost[(unsigned)k]};
         },
         [&](int t, Pair p) {
           const int at = HX ? (t / hx) * ld + Line<HX>::at(t % hx) : t;
-          if (a.xone) {
+          if (xone) {
             A[at] = {p.k.re, T(0)};
           } else {
             p.c.im = -p.c.im;
@@ -1433,8 +1461,10 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
     T k[3], tau[3];
     cell_torque(a, gpm, alpha, bJc, mc, H, k, tau);
     if (MODE == FM_TORQUE || MODE == FM_RKK) {
+      if (MODE == FM_TORQUE || out_r) {  // RK4's last slope is used here only
 #pragma unroll
-      for (int c = 0; c < 3; ++c) out_r[c * N + cell] = k[c];
+        for (int c = 0; c < 3; ++c) out_r[c * N + cell] = k[c];
+      }
       if (MODE == FM_RKK && fwd) {
         // the next stage's combined state, in the order of the combine pass
         T mv[3];
@@ -1452,6 +1482,7 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
         if (a.cnext == 2) {
           const T inv = inv_norm(mv[0] * mv[0] + mv[1] * mv[1] + mv[2] * mv[2]);
           mv[0] *= inv; mv[1] *= inv; mv[2] *= inv;
+          if (a.nfnext && !(fabs(mv[0]) + fabs(mv[1]) + fabs(mv[2]) <= T(3))) *a.nfnext = 1;
         }
         const T ws = (EXT && a.msr) ? a.msr[cell] : T(1);  // transform input M = Ms_i m
 #pragma unroll

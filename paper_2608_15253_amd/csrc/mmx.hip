@@ -365,7 +365,7 @@ struct mmx_ctx {
   // graph replay: library stream, fencing events, step counter, cached graphs
   hipStream_t cap_stream = nullptr;
   hipEvent_t ev_user = nullptr, ev_cap = nullptr;
-  GraphSet heun_graphs, rk_graphs;
+  GraphSet heun_graphs, rk_graphs, rk4_graphs;
   uint64_t epoch = 1;  // configuration epoch: advanced by every setter
   Buf stepdev;
   const unsigned long long* cur_stepdev = nullptr;
@@ -374,6 +374,7 @@ struct mmx_ctx {
     if (cap_stream) (void)hipStreamSynchronize(cap_stream);
     heun_graphs.clear();
     rk_graphs.clear();
+    rk4_graphs.clear();
     if (ev_user) (void)hipEventDestroy(ev_user);
     if (ev_cap) (void)hipEventDestroy(ev_cap);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
@@ -388,7 +389,8 @@ struct mmx_ctx {
   void* arena = nullptr;
   size_t arena_bytes = 0;
   bool arena_owned = false;
-  Buf st;          // RkState
+  Buf st;          // RkState[2]
+  int rk_slot = 0; // the one that launches use
   Buf dts;         // accepted step sizes
   Buf replay;      // dt replay list
   long long dts_cap = 0;
@@ -615,7 +617,7 @@ void arena_walk(mmx_ctx* ctx, F&& take) {
     take(G.nblk_dev, sizeof(int));
     take(G.topo_part, (size_t)G.R * topo_blocks(G) * sizeof(double));
   }
-  take(ctx->st, sizeof(RkState));
+  take(ctx->st, 2 * sizeof(RkState));  // attempts alternate between the two (see k_rk_next)
   take(ctx->dts, (size_t)kDtsCap * sizeof(double));
   take(ctx->replay, (size_t)kDtsCap * sizeof(double));
   take(ctx->Etmp, (size_t)R_total * 6 * sizeof(double));
@@ -752,6 +754,7 @@ struct Epilogue {
   double cn[6] = {0, 0, 0, 0, 0, 0};
   int cnext = 0, cstage = 0;
   void* mnext = nullptr;
+  int check_next = 0;  // a normalised next state is a new state: flag non-finite values
 };
 
 // orthonormal cubic axes from c1 and c2 (c2 orthogonalised against c1)
@@ -1069,12 +1072,10 @@ bool launch_yconv_reg(const Group& G, const YArgs<T>& y, hipStream_t s) {
   }
 }
 
-// stage combine m + dt sum_j c_j k_j (optionally normalised) fused with the x
-// forward transform of the demag convolution when `demag` is set
+// arguments of the combine / x transform kernels for group G on `grid`
 template <typename T>
-mmx_status launch_xfwd(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb, bool demag,
-                       const double* dtdev, double dth, const int* done) {
-  hipStream_t s = ctx->stream;
+XArgs<T> xfwd_args(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb, bool demag,
+                   const double* dtdev, double dth, const int* done, dim3 grid) {
   XArgs<T> x{};
   x.m = mbase;
   x.ncoef = cb.ncoef;
@@ -1101,11 +1102,26 @@ mmx_status launch_xfwd(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb
   x.mL = magic_of(G.L);
   x.mKx = magic_of(G.Kx);
   x.done = done;
-  dim3 grid((G.ny + G.L - 1) / G.L, G.nz, G.R);
-  auto lds_of = [&](int ld) {
-    return demag ? (2 * (size_t)3 * G.L * ld + 2 * G.hx + 1) * cpxb<T>() : size_t(0);
-  };
   x.map = grid_map(grid);
+  return x;
+}
+
+// LDS of a row transform of group G with ld slots per line: two line buffers,
+// the pass twiddles, the split factors
+template <typename T>
+size_t xfwd_lds(const Group& G, int ld) {
+  return (2 * (size_t)3 * G.L * ld + 2 * G.hx + 1) * cpxb<T>();
+}
+
+// stage combine m + dt sum_j c_j k_j (optionally normalised) fused with the x
+// forward transform of the demag convolution when `demag` is set
+template <typename T>
+mmx_status launch_xfwd(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb, bool demag,
+                       const double* dtdev, double dth, const int* done) {
+  hipStream_t s = ctx->stream;
+  dim3 grid((G.ny + G.L - 1) / G.L, G.nz, G.R);
+  const XArgs<T> x = xfwd_args(ctx, G, mbase, cb, demag, dtdev, dth, done, grid);
+  auto lds_of = [&](int ld) { return demag ? xfwd_lds<T>(G, ld) : size_t(0); };
   ProfScope ps(ctx->prof, demag ? "k_xfwd" : "k_combine", s);
   auto go = [&](auto k0, auto k1, auto k6, int ld) {
     if (cb.ncoef == 0)
@@ -1369,8 +1385,9 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
   a.cnext = ep.cnext;
   a.cstage = ep.cstage;
   a.mnext = reinterpret_cast<T*>(ep.mnext);
+  a.nfnext = ep.check_next ? ctx->nfflag.as<int>() : nullptr;
   a.plan_f = G.plan_x;
-  a.st = ctx->st.as<RkState>();
+  a.st = ctx->st.as<RkState>() + ctx->rk_slot;
   a.partial = G.partial.as<double>();
   if (!demag && ctx->hext) {
     a.hext = ctx->hext;
@@ -1444,8 +1461,9 @@ mmx_status rk_begin(mmx_ctx* ctx, double t0, double t_end, double tol, double dt
 // stages 2..7 of one Dormand-Prince attempt for group G from its state mg; the
 // stage-7 evaluation also yields the embedded error estimate (e = b5 - b4)
 template <typename T>
-mmx_status rk_stages(mmx_ctx* ctx, Group& G, T* mg, const double e[7], const StageHook* hook) {
-  RkState* st = ctx->st.as<RkState>();
+mmx_status rk_stages(mmx_ctx* ctx, Group& G, T* mg, const double e[7], const StageHook* hook,
+                     bool ready = false) {
+  RkState* st = ctx->st.as<RkState>() + ctx->rk_slot;
   const int* done = &st->done;
   const double* dtdev = &st->dt;
   // Without learned stages every stage's epilogue also forms the next
@@ -1494,8 +1512,9 @@ mmx_status rk_stages(mmx_ctx* ctx, Group& G, T* mg, const double e[7], const Sta
                                          0, 1.0, dtdev, 0.0, done, ctx->terms & ~MMX_DEMAG);
       ctx->hext = nullptr;
       MMX_TRY(r);
-    } else if (chain && sidx > 1) {
-      // state and half spectrum written by the previous stage's epilogue
+    } else if (chain && (sidx > 1 || ready)) {
+      // state and half spectrum written by the previous stage's epilogue (the
+      // second stage's, if `ready`, by k_rk_next)
       ctx->hd_out = nullptr;
       MMX_TRY(eval_group<T>(ctx, G, reinterpret_cast<const T*>(state[sidx]), Combine{}, ep, 0, 1.0,
                             dtdev, 0.0, done, 0xFFFFFFFFu, true));
@@ -1509,13 +1528,60 @@ mmx_status rk_stages(mmx_ctx* ctx, Group& G, T* mg, const double e[7], const Sta
   return MMX_OK;
 }
 
-// controller decision, then m <- m7 and k1 <- k7 if the attempt was accepted
+// k_rk_next for every group: from the attempt in the current state slot to the
+// next attempt's second stage, in the other slot (which becomes the current)
+template <typename T>
+mmx_status rk_next(mmx_ctx* ctx, T* mb, const double* replay) {
+  RkState* st = ctx->st.as<RkState>();
+  const int from = ctx->rk_slot, to = 1 - from;
+  int lead = 1;
+  for (auto& gp : ctx->groups) {
+    Group& G = *gp;
+    T* mg = mb + G.off;
+    Combine cb;
+    cb.ncoef = 1;
+    cb.coef[0] = DP_A[1][0];
+    cb.mout = G.ms.p;
+    const dim3 grid((G.ny + G.L - 1) / G.L, G.nz, G.R);
+    NextArgs<T> a{};
+    a.x = xfwd_args<T>(ctx, G, mg, cb, true, nullptr, 0.0, nullptr, grid);
+    a.in = st + from;
+    a.out = st + to;
+    a.replay = replay;
+    a.dts = ctx->dts.as<double>();
+    a.dts_cap = ctx->dts_cap;
+    a.m = mg;
+    a.k1 = G.k[0].as<T>();
+    a.m7 = G.m7.as<T>();
+    a.k7 = G.k[6].as<T>();
+    a.lead = lead;
+    lead = 0;
+    auto lds_of = [&](int ld) { return xfwd_lds<T>(G, ld); };
+    auto go = [&](auto kern, int ld) { kern<<<grid, kBlock, lds_of(ld), ctx->stream>>>(a); };
+    switch (fixed_hx<T>(G, lds_of)) {
+      case 32: go(k_rk_next<T, 32>, Line<32>::LD); break;
+      case 64: go(k_rk_next<T, 64>, Line<64>::LD); break;
+      case 128: go(k_rk_next<T, 128>, Line<128>::LD); break;
+      case 256: go(k_rk_next<T, 256>, Line<256>::LD); break;
+      default: go(k_rk_next<T, 0>, G.hx); break;
+    }
+    HIP_TRY(hipGetLastError());
+  }
+  ctx->rk_slot = to;
+  return MMX_OK;
+}
+
+// controller decision, then m <- m7 and k1 <- k7 if the attempt was accepted;
+// leaves the new state in slot 0
 template <typename T>
 mmx_status rk_finish(mmx_ctx* ctx, T* mb, const double* replay) {
   RkState* st = ctx->st.as<RkState>();
+  const RkState* from = st + ctx->rk_slot;
+  ctx->rk_slot = 0;
   {
     ProfScope psc(ctx->prof, "k_rk_controller", ctx->stream);
-    k_rk_controller<<<1, 1, 0, ctx->stream>>>(st, replay, ctx->dts.as<double>(), ctx->dts_cap);
+    k_rk_controller<<<1, 1, 0, ctx->stream>>>(from, st, replay, ctx->dts.as<double>(),
+                                              ctx->dts_cap);
     HIP_TRY(hipGetLastError());
   }
   for (auto& gp : ctx->groups) {
@@ -1609,6 +1675,7 @@ mmx_status rk45_impl(mmx_ctx* ctx, void* m, double t0, double t_end, double tol,
     key.p[5] = ctx->Etmp.p;
     key.i[0] = cap;
     key.i[1] = ctx->dts_cap;
+    key.i[2] = ctx->noprec;  // the relaxer sets it without advancing the epoch
     GraphSet& gs = ctx->rk_graphs;
     if (!gs.valid || !(gs.key == key)) {
       HIP_TRY(hipStreamSynchronize(cs));
@@ -1616,10 +1683,25 @@ mmx_status rk45_impl(mmx_ctx* ctx, void* m, double t0, double t_end, double tol,
       gs.exec.assign(1, nullptr);
       gs.key = key;
       gs.valid = true;
-      MMX_TRY(capture_graph(ctx, [&]() -> mmx_status {
-        for (int i = 0; i < chunk; ++i) MMX_TRY(one_step());
+      const double* rp = replay ? ctx->replay.as<double>() : nullptr;
+      // with the demag term (whose stages are chained) and no energy trace
+      // (which reads the committed state), the attempts of a chunk are joined
+      // by one pass each
+      const bool joined = (ctx->terms & MMX_DEMAG) && !trace;
+      const mmx_status st_cap = capture_graph(ctx, [&]() -> mmx_status {
+        for (int i = 0; i < chunk; ++i) {
+          if (!joined) {
+            MMX_TRY(one_step());
+            continue;
+          }
+          for (auto& gp : ctx->groups)
+            MMX_TRY(rk_stages<T>(ctx, *gp, mb + gp->off, e, nullptr, i > 0));
+          MMX_TRY(i + 1 < chunk ? rk_next<T>(ctx, mb, rp) : rk_finish<T>(ctx, mb, rp));
+        }
         return MMX_OK;
-      }, &gs.exec[0]));
+      }, &gs.exec[0]);
+      ctx->rk_slot = 0;
+      MMX_TRY(st_cap);
     }
     HIP_TRY(hipEventRecord(ctx->ev_user, s));
     HIP_TRY(hipStreamWaitEvent(cs, ctx->ev_user, 0));
@@ -1658,6 +1740,39 @@ mmx_status ensure_graph_stream(mmx_ctx* ctx) {
   if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
   if (!ctx->ev_user) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_user, hipEventDisableTiming));
   if (!ctx->ev_cap) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_cap, hipEventDisableTiming));
+  return MMX_OK;
+}
+
+// n_steps = a sum of runs of 2^i steps (i < kHeunGraphs, largest first), each
+// run length captured once by body(2^i) and replayed, on the library's stream
+// between two fences of the caller's.
+template <typename F>
+mmx_status replay_runs(mmx_ctx* ctx, GraphSet& gs, const GraphKey& key, int64_t n_steps, F&& body) {
+  MMX_TRY(ensure_graph_stream(ctx));
+  hipStream_t user = ctx->stream, cs = ctx->cap_stream;
+  if (!gs.valid || !(gs.key == key)) {
+    HIP_TRY(hipStreamSynchronize(cs));
+    gs.clear();
+    gs.exec.assign(kHeunGraphs, nullptr);
+    gs.key = key;
+    gs.valid = true;
+  }
+  std::vector<int> runs;
+  for (int64_t left = n_steps; left > 0;) {
+    int i = kHeunGraphs - 1;
+    while ((int64_t(1) << i) > left) --i;
+    runs.push_back(i);
+    left -= int64_t(1) << i;
+  }
+  for (int i : runs) {
+    if (gs.exec[i]) continue;
+    MMX_TRY(capture_graph(ctx, [&]() -> mmx_status { return body(int64_t(1) << i); }, &gs.exec[i]));
+  }
+  HIP_TRY(hipEventRecord(ctx->ev_user, user));
+  HIP_TRY(hipStreamWaitEvent(cs, ctx->ev_user, 0));
+  for (int i : runs) HIP_TRY(hipGraphLaunch(gs.exec[i], cs));
+  HIP_TRY(hipEventRecord(ctx->ev_cap, cs));
+  HIP_TRY(hipStreamWaitEvent(user, ctx->ev_cap, 0));
   return MMX_OK;
 }
 
@@ -2077,11 +2192,41 @@ mmx_status rk4_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps) {
   if (ctx->terms & MMX_THERMAL) return fail(MMX_EUNSUP, "thermal field with RK4");
   ctx->rk_valid = 0;
   for (auto& gp : ctx->groups) MMX_TRY(ensure_rk_buffers<T>(*gp));
+  if (n_steps == 0) return MMX_OK;
   T* mb = reinterpret_cast<T*>(m);
-  for (int64_t i = 0; i < n_steps; ++i) {
+  const double w[4] = {1.0 / 6.0, 1.0 / 3.0, 1.0 / 3.0, 1.0 / 6.0};
+  // With the demag term each stage's epilogue forms the next stage's state
+  // and its x transform, the last one's the new state (as in rk_stages): eight
+  // launches per step instead of thirteen.  The stage states alternate
+  // between two buffers, since a stage reads its own state's neighbours.
+  const bool chain = (ctx->terms & MMX_DEMAG) != 0;
+  auto one_step = [&]() -> mmx_status {
     for (auto& gp : ctx->groups) {
       Group& G = *gp;
       T* mg = mb + G.off;
+      if (chain) {
+        T* state[5] = {mg, G.ms.as<T>(), G.ms2.as<T>(), G.ms.as<T>(), mg};
+        for (int st = 0; st < 4; ++st) {
+          Epilogue e;
+          e.mode = FM_RKK;
+          e.out = st < 3 ? G.k[st].p : nullptr;
+          e.fwd = 1;
+          e.m0 = mg;
+          e.cstage = st;
+          e.mnext = state[st + 1];
+          if (st < 3) {
+            e.cn[st] = st == 2 ? 1.0 : 0.5;
+            e.cnext = 1;
+          } else {
+            for (int j = 0; j < 4; ++j) e.cn[j] = w[j];
+            e.cnext = 2;
+            e.check_next = 1;
+          }
+          MMX_TRY(eval_group<T>(ctx, G, state[st], Combine{}, e, 0, dt, nullptr, dt, nullptr,
+                                0xFFFFFFFFu, true));
+        }
+        continue;
+      }
       Epilogue e;
       e.mode = FM_RKK;
       e.out = G.k[0].p;
@@ -2097,7 +2242,6 @@ mmx_status rk4_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps) {
       }
       Combine fc;
       fc.ncoef = 4;
-      const double w[4] = {1.0 / 6.0, 1.0 / 3.0, 1.0 / 3.0, 1.0 / 6.0};
       for (int j = 0; j < 4; ++j) {
         fc.coef[j] = w[j];
         fc.kidx[j] = j;
@@ -2107,8 +2251,34 @@ mmx_status rk4_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps) {
       fc.mout = mg;
       MMX_TRY(launch_xfwd<T>(ctx, G, mg, fc, false, nullptr, dt, nullptr));
     }
+    return MMX_OK;
+  };
+  if (chain) {
+    for (auto& gp : ctx->groups) {
+      Group& G = *gp;
+      if (!G.demag_built) return fail(MMX_ESTATE, "mmx_build_demag has not been called");
+      MMX_TRY(launch_xfwd<T>(ctx, G, mb + G.off, Combine{}, true, nullptr, dt, nullptr));
+    }
   }
-  return MMX_OK;
+  // a caller that captures its stream (the null stream cannot be) gets plain launches
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (ctx->stream) HIP_TRY(hipStreamIsCapturing(ctx->stream, &cap));
+  if (ctx->prof.on || cap != hipStreamCaptureStatusNone) {
+    for (int64_t i = 0; i < n_steps; ++i) MMX_TRY(one_step());
+    return MMX_OK;
+  }
+  // runs of 2^i captured steps, kept for later calls, as in heun_impl.  Launched
+  // one by one, a kernel of a small grid waits for its arguments, which
+  // are then in host memory (260 ns for each line read, 70 ns in a graph)
+  GraphKey key;
+  key.epoch = ctx->epoch;
+  key.p[0] = m;
+  key.d = dt;
+  return replay_runs(ctx, ctx->rk4_graphs, key, n_steps,
+                     [&](int64_t n) -> mmx_status {
+                       for (int64_t i = 0; i < n; ++i) MMX_TRY(one_step());
+                       return MMX_OK;
+                     });
 }
 
 // max over all replicas and cells of |dm/dt| (synchronous)
@@ -2337,36 +2507,42 @@ mmx_status apply_tiles(Group& G, int L, int Wy, int Wz) {
   return MMX_OK;
 }
 
+// Time of one field evaluation of group G with its current tiles.  A few
+// evaluations are captured and replayed, the second replay timed: one
+// evaluation of a small grid takes 20 us, as long as its plain launches take
+// the host, which hid differences of a half between tiles (64 x 64 x 16: eight
+// rows per workgroup, the slowest, were chosen).
 template <typename T>
 mmx_status time_eval(mmx_ctx* ctx, Group& G, float& ms) {
-  hipEvent_t a, b;
-  HIP_TRY(hipEventCreate(&a));
-  HIP_TRY(hipEventCreate(&b));
+  MMX_TRY(ensure_graph_stream(ctx));
+  hipStream_t cs = ctx->cap_stream;
   Epilogue ep;
   ep.mode = FM_FIELD;
   ep.out = G.k[0].p;
-  mmx_status st = MMX_OK;
-  float best = 1e30f;
-  // two repetitions of a few evaluations, the first to warm caches: one
-  // evaluation of a small grid takes 20 us, as long as its launches take the
-  // host, and the spread of single ones hid differences of a third between
-  // tiles
-  const int evals = (size_t)G.R * G.N <= (1u << 19) ? 5 : 2;
-  for (int rep = 0; rep < 2 && st == MMX_OK; ++rep) {
-    (void)hipEventRecord(a, ctx->stream);
-    for (int i = 0; i < evals && st == MMX_OK; ++i)
-      st = eval_group<T>(ctx, G, G.ms.as<T>(), Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
-                         ctx->terms & ~MMX_THERMAL);
-    (void)hipEventRecord(b, ctx->stream);
-    (void)hipEventSynchronize(b);
-    float t = 0;
-    (void)hipEventElapsedTime(&t, a, b);
-    if (rep > 0) best = std::min(best, t / evals);
-  }
-  (void)hipEventDestroy(a);
-  (void)hipEventDestroy(b);
-  ms = best;
-  return st;
+  const int evals = (size_t)G.R * G.N <= (1u << 19) ? 4 : 1;
+  hipGraphExec_t exec = nullptr;
+  MMX_TRY(capture_graph(ctx, [&]() -> mmx_status {
+    for (int i = 0; i < evals; ++i)
+      MMX_TRY(eval_group<T>(ctx, G, G.ms.as<T>(), Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
+                            ctx->terms & ~MMX_THERMAL));
+    return MMX_OK;
+  }, &exec));
+  hipEvent_t a = nullptr, b = nullptr;
+  hipError_t e = hipEventCreate(&a);
+  if (e == hipSuccess) e = hipEventCreate(&b);
+  if (e == hipSuccess) e = hipGraphLaunch(exec, cs);  // warms the caches
+  if (e == hipSuccess) e = hipEventRecord(a, cs);
+  if (e == hipSuccess) e = hipGraphLaunch(exec, cs);
+  if (e == hipSuccess) e = hipEventRecord(b, cs);
+  if (e == hipSuccess) e = hipEventSynchronize(b);
+  float t = 0;
+  if (e == hipSuccess) e = hipEventElapsedTime(&t, a, b);
+  if (a) (void)hipEventDestroy(a);
+  if (b) (void)hipEventDestroy(b);
+  (void)hipGraphExecDestroy(exec);
+  HIP_TRY(e);
+  ms = t / evals;
+  return MMX_OK;
 }
 
 template <typename T>
@@ -2376,6 +2552,7 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
     Group& G = *gp;
     if (!G.demag_built) continue;
     HIP_TRY(hipMemsetAsync(G.ms.p, 0, G.ms.bytes, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));  // time_eval runs on the library's stream
     const int cand[] = {1, 2, 4, 8, 16, 32};
     int bestL = G.L, bestW = G.Wy, bestWz = G.Wz;
     float bt = 1e30f;

@@ -68,7 +68,7 @@ __global__ void k_line_fft(cpx<double>* data, long os, long is, long stride, Fft
   const long base = (long)blockIdx.y * os + (long)blockIdx.x * is;
   for (int k = threadIdx.x; k < plan.n; k += blockDim.x) A[k] = data[base + k * stride];
   __syncthreads();
-  const cpx<double>* X = lds_fft<double, false>(A, Bf, 1, plan, tw);
+  const cpx<double>* X = lds_fft<double, false, 128>(A, Bf, 1, plan, tw);
   for (int k = threadIdx.x; k < plan.n; k += blockDim.x) data[base + k * stride] = X[k];
 }
 
@@ -93,48 +93,177 @@ __global__ void k_compress(T* Nt, const cpx<double>* K, int Px, int Py, int Pz, 
 // ---------------------------------------------------------------------------
 // integrator bookkeeping
 // ---------------------------------------------------------------------------
-__global__ void k_rk_controller(RkState* st, const double* replay, double* dts, long long dts_cap) {
-  if (st->done) return;
-  double err = __longlong_as_double((long long)st->err_bits);
-  if (st->nonfinite) err = __builtin_nan("");
-  st->err_bits = 0ull;
-  st->nonfinite = 0;
-  st->last_err = err;
-  const double dt = st->dt;
-  bool accept;
+// The controller's decision on the attempt that ended in state s: the state of
+// the next attempt, and whether this one is accepted.
+__device__ inline double rk_error(const RkState& s) {
+  return s.nonfinite ? __builtin_nan("") : __longlong_as_double((long long)s.err_bits);
+}
+__device__ inline bool rk_accept(const RkState& s, const double* replay) {
+  return replay || rk_error(s) <= s.tol;
+}
+__device__ inline RkState rk_decide(const RkState& s, const double* replay) {
+  RkState n = s;
+  const double err = rk_error(s);
+  const bool accept = rk_accept(s, replay);
+  n.err_bits = 0ull;
+  n.nonfinite = 0;
+  n.last_err = err;
   double next;
   if (replay) {
-    accept = true;
-    st->replay_idx += 1;
-    next = (st->replay_idx < st->n_replay) ? replay[st->replay_idx] : 0.0;
+    n.replay_idx = s.replay_idx + 1;
+    next = (n.replay_idx < s.n_replay) ? replay[n.replay_idx] : 0.0;
   } else {
-    double fac;
-    if (!(err == err)) { fac = 0.2; accept = false; }
-    else {
-      accept = err <= st->tol;
-      fac = (err == 0.0) ? 5.0 : fmin(5.0, fmax(0.2, 0.9 * pow(st->tol / err, 0.2)));
-    }
-    next = fmin(dt * fac, st->dt_max);
+    double fac = 0.2;
+    if (err == err)
+      fac = (err == 0.0) ? 5.0 : fmin(5.0, fmax(0.2, 0.9 * pow(s.tol / err, 0.2)));
+    next = fmin(s.dt * fac, s.dt_max);
   }
   if (accept) {
-    if (st->accepted < dts_cap) dts[st->accepted] = dt;
-    st->accepted += 1;
-    st->t = (st->final_flag && !replay) ? st->t_end : st->t + dt;
+    n.accepted = s.accepted + 1;
+    n.t = (s.final_flag && !replay) ? s.t_end : s.t + s.dt;
   } else {
-    st->rejected += 1;
+    n.rejected = s.rejected + 1;
   }
-  st->accepted_flag = accept ? 1 : 0;
+  n.accepted_flag = accept ? 1 : 0;
   if (replay) {
-    st->dt = next;
-    if (st->replay_idx >= st->n_replay) st->done = 1;
+    n.dt = next;
+    if (n.replay_idx >= n.n_replay) n.done = 1;
+    return n;
+  }
+  n.dt_prop = next;
+  n.final_flag = (n.t + next >= n.t_end) ? 1 : 0;
+  if (n.final_flag) next = n.t_end - n.t;
+  n.dt = next;
+  if (n.t >= n.t_end) n.done = 1;
+  else if (next < n.dt_min) { n.done = 1; n.dtmin_hit = 1; }
+  return n;
+}
+
+// the decision alone: from *in to *out (may be the same)
+__global__ void k_rk_controller(const RkState* in, RkState* out, const double* replay, double* dts,
+                                long long dts_cap) {
+  const RkState s = *in;
+  if (s.done) {
+    if (out != in) *out = s;
     return;
   }
-  st->dt_prop = next;
-  st->final_flag = (st->t + next >= st->t_end) ? 1 : 0;
-  if (st->final_flag) next = st->t_end - st->t;
-  st->dt = next;
-  if (st->t >= st->t_end) st->done = 1;
-  else if (next < st->dt_min) { st->done = 1; st->dtmin_hit = 1; }
+  if (rk_accept(s, replay) && s.accepted < dts_cap) dts[s.accepted] = s.dt;
+  *out = rk_decide(s, replay);
+}
+
+// Between two attempts in one pass: the decision on the attempt in *in, its
+// commit (m <- m7, k1 <- k7 if accepted) and the next attempt's second-stage state
+// m + dt a21 k1 with its x transform (the work of k_xfwd; x.m = m, x.kk[0] =
+// k1).  The first wave of every workgroup computes the decision for its
+// workgroup; the first workgroup of the leading group writes the new state
+// to *out, which is not *in, so that every reader sees the old one.
+// Separately (controller on one thread, copy of both arrays, combine) these
+// took 19 of the 200 us of an attempt on the 512 x 512 film.
+template <typename T>
+struct NextArgs {
+  XArgs<T> x;
+  const RkState* in;
+  RkState* out;
+  const double* replay;
+  double* dts;
+  long long dts_cap;
+  T* m;
+  T* k1;
+  const T* m7;
+  const T* k7;
+  int lead;
+};
+
+template <typename T, int HX>
+__global__ void __launch_bounds__(kBlock) k_rk_next(NextArgs<T> a) {
+  const XArgs<T>& x = a.x;
+  const RkState s = *a.in;
+  const bool first = blockIdx.x + blockIdx.y + blockIdx.z == 0 && threadIdx.x == 0 && a.lead;
+  if (s.done) {
+    if (first) *a.out = s;
+    return;
+  }
+  const bool accept = rk_accept(s, a.replay);
+  extern __shared__ unsigned char smem_raw[];
+  __shared__ double dt_next;
+  __shared__ int done_next;
+  cpx<T>* A = reinterpret_cast<cpx<T>*>(smem_raw);
+  const int hx = HX ? HX : x.hx, ld = HX ? Line<HX>::LD : hx, L = x.L, nl = 3 * L;
+  cpx<T>* Bf = A + nl * ld;
+  cpx<T>* tw = Bf + nl * ld;
+  cpx<T>* wpost = tw + hx;
+  auto tw_m = table_mover<T>(tw, x.tw, hx);
+  auto wp_m = table_mover<T>(wpost, x.wpost, hx + 1);
+  tw_m.issue();
+  wp_m.issue();
+  if (threadIdx.x < 64) {
+    const RkState n = rk_decide(s, a.replay);
+    if (threadIdx.x == 0) {
+      dt_next = n.dt;
+      done_next = n.done;
+    }
+    if (first) {
+      if (accept && s.accepted < a.dts_cap) a.dts[s.accepted] = s.dt;
+      *a.out = n;
+    }
+  }
+  int bx, by, bz;
+  xcd_block(x.map, bx, by, bz);
+  const int r = bz, z = by, y0 = bx * L;
+  const size_t rb = (size_t)r * 3 * x.N;
+  const unsigned N = (unsigned)x.N;
+  const int npair = x.xone ? 1 : (x.nx + 1) / 2;
+  const int kw = x.kw;
+  const T* __restrict__ ms = (accept ? a.m7 : a.m) + rb;
+  const T* __restrict__ ks = (accept ? a.k7 : a.k1) + rb;
+  __syncthreads();
+  const T dt = (T)dt_next;
+  for (int t = threadIdx.x; t < L * kw; t += kBlock) {
+    const int l = mdiv(t, x.mkw), k = t - l * kw, y = y0 + l;
+    cpx<T> v[3] = {{0, 0}, {0, 0}, {0, 0}};
+    if (y < x.ny && k < npair) {
+      const bool two = 2 * k + 1 < x.nx;
+      const unsigned c0 = (unsigned)(2 * k) + (unsigned)x.nx * (unsigned)(y + x.ny * z);
+      const unsigned cell[2] = {c0, two ? c0 + 1 : c0};
+      T mv[2][3], pk[2][3];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        ld3(ms, N, cell[h], mv[h]);
+        ld3(ks, N, cell[h], pk[h]);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h == 1 && !two) break;
+        if (accept) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            a.m[rb + (size_t)c * x.N + cell[h]] = mv[h][c];
+            a.k1[rb + (size_t)c * x.N + cell[h]] = pk[h][c];
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) mv[h][c] += dt * x.coef[0] * pk[h][c];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x.mout[rb + (size_t)c * x.N + cell[h]] = mv[h][c];
+        if (x.msr) {  // the convolution acts on M = Ms_i m
+          const T w = x.msr[cell[h]];
+          mv[h][0] *= w; mv[h][1] *= w; mv[h][2] *= w;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          if (h == 0) v[c].re = mv[h][c]; else v[c].im = mv[h][c];
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) A[(c * L + l) * ld + Line<HX>::at(k)] = v[c];
+  }
+  if (done_next) return;  // the run ended with this attempt: nothing follows
+  tw_m.finish();
+  wp_m.finish();
+  __syncthreads();
+  const cpx<T>* X = line_fft<T, false, HX>(A, Bf, nl, x.plan, tw);
+  xfwd_store<T, HX>(X, wpost, x.S, r, z, y0, L, hx, x.Kx, x.ny, x.nz, x.Sy, x.xone, x.mL, x.mKx);
 }
 
 template <typename T>

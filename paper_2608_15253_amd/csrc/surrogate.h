@@ -128,7 +128,8 @@ mmx_status rk45_surrogate_impl(mmx_ctx* ctx, mmx_fno* f, const float* prm, void*
       MMX_TRY(rk_stages<float>(ctx, G, mb, e, &hook));
       {
         ProfScope psc(ctx->prof, "k_rk_controller", s);
-        k_rk_controller<<<1, 1, 0, s>>>(ctx->st.as<RkState>(), nullptr, ctx->dts.as<double>(),
+        k_rk_controller<<<1, 1, 0, s>>>(ctx->st.as<RkState>(), ctx->st.as<RkState>(), nullptr,
+                                     ctx->dts.as<double>(),
                                         ctx->dts_cap);
         HIP_TRY(hipGetLastError());
       }
