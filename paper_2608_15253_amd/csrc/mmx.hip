@@ -321,6 +321,22 @@ struct ProfScope {
 
 }  // namespace
 
+// Parts of the staged groups that a run of Heun steps is split into.  The four
+// or five passes of a step, and the next step, reread what the one before
+// wrote: a part whose spectrum and states stay in the 256 MB memory-side
+// cache is advanced through a whole captured run before the next part starts.
+// kRunBytes is the working set in flight, parts of half of it on two streams, so
+// that one part's kernels fill the chip while the other's start and drain.
+// Measured per step, films of 64 x 64 (198 KB per replica): 1024 replicas in one part
+// 244.6 us, two on two streams 222, two of 104 MB in turn 267; 2048
+// replicas 600 in one part (its 400 MB miss the cache), 492 in 208 MB parts in turn,
+// 453 in 104 MB parts on two streams, 523 in 130 MB parts; three streams the
+// same, four slower.  512 replicas (101 MB) 134 -> 128 in two; 256 (50 MB) 90 -> 86,
+// but the uneven groups' 13 and 50 MB, split, 1052 -> 1110: hence kSplitBytes.
+constexpr size_t kRunBytes = size_t(208) << 20;
+constexpr size_t kSplitBytes = size_t(64) << 20;  // smaller groups are one part
+constexpr int kRunStreams = 2;
+
 // Captured step sequences kept between calls: Heun / rotation runs of 2^i
 // steps (i < kHeunGraphs) and chunks of RK45 attempts, each valid for the
 // call signature it was captured with (the context's configuration epoch,
@@ -365,6 +381,9 @@ struct mmx_ctx {
   // graph replay: library stream, fencing events, step counter, cached graphs
   hipStream_t cap_stream = nullptr;
   hipEvent_t ev_user = nullptr, ev_cap = nullptr;
+  // streams and events that captures fork to and join from (run_concurrent)
+  hipStream_t side[kRunStreams - 1] = {};
+  hipEvent_t ev_fork = nullptr, ev_join[kRunStreams - 1] = {};
   GraphSet heun_graphs, rk_graphs, rk4_graphs;
   uint64_t epoch = 1;  // configuration epoch: advanced by every setter
   Buf stepdev;
@@ -377,6 +396,11 @@ struct mmx_ctx {
     rk4_graphs.clear();
     if (ev_user) (void)hipEventDestroy(ev_user);
     if (ev_cap) (void)hipEventDestroy(ev_cap);
+    if (ev_fork) (void)hipEventDestroy(ev_fork);
+    for (auto e : ev_join)
+      if (e) (void)hipEventDestroy(e);
+    for (auto t : side)
+      if (t) (void)hipStreamDestroy(t);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     if (arena && arena_owned) (void)hipFree(arena);
   }
@@ -1740,7 +1764,39 @@ mmx_status ensure_graph_stream(mmx_ctx* ctx) {
   if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
   if (!ctx->ev_user) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_user, hipEventDisableTiming));
   if (!ctx->ev_cap) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_cap, hipEventDisableTiming));
+  if (!ctx->ev_fork) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
+  for (int i = 0; i < kRunStreams - 1; ++i) {
+    if (!ctx->side[i])
+      HIP_TRY(hipStreamCreateWithFlags(&ctx->side[i], hipStreamNonBlocking));
+    if (!ctx->ev_join[i])
+      HIP_TRY(hipEventCreateWithFlags(&ctx->ev_join[i], hipEventDisableTiming));
+  }
   return MMX_OK;
+}
+
+// During a capture on ctx->stream: the chains body(0) .. body(n - 1), which do not
+// depend on each other, on up to kRunStreams streams forked from it and joined
+// to it again.
+template <typename F>
+mmx_status run_concurrent(mmx_ctx* ctx, size_t n, F&& body) {
+  if (n == 1) return body(0);
+  hipStream_t main = ctx->stream;
+  const int ns = (int)std::min<size_t>(n, kRunStreams);
+  HIP_TRY(hipEventRecord(ctx->ev_fork, main));
+  for (int i = 1; i < ns; ++i) HIP_TRY(hipStreamWaitEvent(ctx->side[i - 1], ctx->ev_fork, 0));
+  mmx_status st = MMX_OK;
+  for (size_t p = 0; p < n && st == MMX_OK; ++p) {
+    const int i = (int)(p % ns);
+    ctx->stream = i ? ctx->side[i - 1] : main;
+    st = body(p);
+  }
+  ctx->stream = main;
+  // joined even after an error, so that the capture can end
+  for (int i = 1; i < ns; ++i) {
+    HIP_TRY(hipEventRecord(ctx->ev_join[i - 1], ctx->side[i - 1]));
+    HIP_TRY(hipStreamWaitEvent(main, ctx->ev_join[i - 1], 0));
+  }
+  return st;
 }
 
 // n_steps = a sum of runs of 2^i steps (i < kHeunGraphs, largest first), each
@@ -1922,6 +1978,53 @@ mmx_status refill_begin(mmx_ctx* ctx, Group& G, const RefillArgs& rf, int roff, 
   return MMX_OK;
 }
 
+// Replicas r0 .. r0 + n - 1 of group gi as a group of their own: the same
+// geometry, tables and coefficients, the buffers from replica r0 on.
+struct ReplicaView {
+  Group g;
+  int gi, r0;
+};
+
+template <typename T>
+ReplicaView replica_view(const Group& G, int gi, int r0, int n) {
+  ReplicaView v{G, gi, r0};
+  Group& V = v.g;
+  V.R = n;
+  auto shift = [&](Buf& b, size_t per_replica) {
+    b.p = static_cast<unsigned char*>(b.p) + r0 * per_replica;
+    b.bytes = n * per_replica;
+  };
+  const size_t state = (size_t)3 * G.N * sizeof(T);
+  const size_t spec = (size_t)3 * G.nz * G.Sy * G.Kx * cpxb<T>();
+  for (Buf* b : {&V.ms, &V.ms2, &V.m7}) shift(*b, state);
+  for (Buf& b : V.k) shift(b, state);
+  for (Buf* b : {&V.S, &V.S_init}) shift(*b, spec);
+  for (Buf* b : {&V.Trep, &V.Jrep}) shift(*b, sizeof(double));
+  shift(V.seeds, sizeof(uint64_t));
+  shift(V.tstart, sizeof(unsigned long long));
+  for (Buf* b : {&V.tgen, &V.tflag}) shift(*b, sizeof(int));
+  shift(V.partial, (size_t)G.ny * G.nz * 5 * sizeof(double));
+  return v;
+}
+
+template <typename T>
+std::vector<ReplicaView> run_parts(const mmx_ctx* ctx, const std::vector<int>& staged, bool rot) {
+  std::vector<ReplicaView> parts;
+  for (int gi : staged) {
+    const Group& G = *ctx->groups[gi];
+    const size_t per = (size_t)3 * G.nz * G.Sy * G.Kx * cpxb<T>() +
+                       (size_t)(rot ? 3 : 2) * 3 * G.N * sizeof(T);
+    const size_t most = std::max<size_t>(1, kRunBytes / kRunStreams / per);
+    int np = (int)(((size_t)G.R + most - 1) / most);
+    if (G.R * per >= kSplitBytes) np = std::max(np, std::min(kRunStreams, G.R));
+    for (int p = 0; p < np; ++p) {
+      const int r0 = (int)((long long)G.R * p / np), r1 = (int)((long long)G.R * (p + 1) / np);
+      parts.push_back(replica_view<T>(G, gi, r0, r1 - r0));
+    }
+  }
+  return parts;
+}
+
 template <typename T>
 mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t step0,
                      void* tsw, int rot = 0, const RefillArgs* rf = nullptr) {
@@ -2004,15 +2107,18 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
       HIP_TRY(hipGetLastError());
     }
   }
-  // one Heun step of every staged group on ctx->stream; with ctx->cur_stepdev
-  // set the kernels take the step index *cur_stepdev + step (step: the offset
-  // within a captured run, after which the counter is advanced once)
-  auto one_step = [&](uint64_t step) -> mmx_status {
+  std::vector<ReplicaView> parts = run_parts<T>(ctx, staged, rot != 0);
+  // one Heun step of a part of a staged group on ctx->stream; with
+  // ctx->cur_stepdev set the kernels take the step index *cur_stepdev + step
+  // (step: the offset within a captured run, after which the counter is
+  // advanced once)
+  auto one_step = [&](ReplicaView& part, uint64_t step) -> mmx_status {
     hipStream_t st = ctx->stream;
-    for (int gi : staged) {
-      Group& G = *ctx->groups[gi];
-      const int roff = roffs[gi];
-      T* mg = mb + G.off;
+    {
+      Group& G = part.g;
+      const int gi = part.gi, roff = roffs[gi] + part.r0;
+      const size_t moff = G.off + (size_t)part.r0 * 3 * G.N;
+      T* mg = mb + moff;
       // each epilogue x-transforms the state it writes, so both field
       // evaluations start from a ready half spectrum (the first one of the
       // call is prepared below)
@@ -2058,7 +2164,7 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
         // small rather than wide
         const dim3 grid(1, (unsigned)G.R);
         k_refill_copy<T><<<grid, 256, 0, st>>>(
-            G.tflag.as<int>(), mg, reinterpret_cast<const T*>(rf->m_init) + G.off, n,
+            G.tflag.as<int>(), mg, reinterpret_cast<const T*>(rf->m_init) + moff, n,
             ns ? G.S.as<cpx<T>>() : nullptr, ns ? G.S_init.as<cpx<T>>() : nullptr, ns);
         HIP_TRY(hipGetLastError());
       }
@@ -2149,14 +2255,17 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
       if (gs.exec[i]) continue;
       ctx->cur_stepdev = sd;
       const mmx_status st = capture_graph(ctx, [&]() -> mmx_status {
-        for (int j = 0; j < (1 << i); ++j) MMX_TRY(one_step((uint64_t)j));
+        MMX_TRY(run_concurrent(ctx, parts.size(), [&](size_t p) -> mmx_status {
+          for (int j = 0; j < (1 << i); ++j) MMX_TRY(one_step(parts[p], (uint64_t)j));
+          return MMX_OK;
+        }));
         k_inc_u64<<<1, 1, 0, ctx->stream>>>(sd, 1ull << i);
         HIP_TRY(hipGetLastError());
         return MMX_OK;
       }, &gs.exec[i]);
       ctx->cur_stepdev = nullptr;
       MMX_TRY(st);
-      for (int gi : staged) gs.nblk[gi] = ctx->groups[gi]->nblk_last;
+      for (const ReplicaView& v : parts) gs.nblk[v.gi] = v.g.nblk_last;
     }
     HIP_TRY(hipEventRecord(ctx->ev_user, user));
     HIP_TRY(hipStreamWaitEvent(cs, ctx->ev_user, 0));
@@ -2165,16 +2274,17 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
     for (int i : runs) HIP_TRY(hipGraphLaunch(gs.exec[i], cs));
     HIP_TRY(hipEventRecord(ctx->ev_cap, cs));
     HIP_TRY(hipStreamWaitEvent(user, ctx->ev_cap, 0));
-    for (int gi : staged) ctx->groups[gi]->nblk_last = gs.nblk[gi];
+    for (ReplicaView& v : parts) v.g.nblk_last = gs.nblk[v.gi];
   } else {
-    for (int64_t i = 0; i < n_steps; ++i) MMX_TRY(one_step(step0 + (uint64_t)i));
+    for (int64_t i = 0; i < n_steps; ++i)
+      for (ReplicaView& v : parts) MMX_TRY(one_step(v, step0 + (uint64_t)i));
   }
-  for (int gi : staged) {  // the last step's switching check
-    if (!folds[gi]) continue;
-    Group& G = *ctx->groups[gi];
+  for (ReplicaView& v : parts) {  // the last step's switching check
+    if (!folds[v.gi]) continue;
+    const Group& G = v.g;
     ProfScope ps(ctx->prof, "k_switch_reduce", s);
     k_switch_reduce<<<(G.R + 63) / 64, 64, 0, s>>>(G.partial.as<double>(), G.nblk_last, G.R, G.N,
-                                                   tsw_d + roffs[gi],
+                                                   tsw_d + roffs[v.gi] + v.r0,
                                                    (unsigned long long)(step0 + (uint64_t)n_steps),
                                                    nullptr, dt);
     HIP_TRY(hipGetLastError());
