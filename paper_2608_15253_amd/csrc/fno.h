@@ -39,128 +39,123 @@ struct ConvArgs {
   int M, K, P, trans, epi;
 };
 
-// Y[b][m][p] = sum_k W[m][k] X[b][k][p] + bias[m], then the epilogue.
-// Workgroup: sample blockIdx.y, pixels [PT blockIdx.x, +PT); on the matrix
-// cores wave w owns PT / 64 tiles of 16 pixels and every 16-row tile of the
-// output channels (64-pixel workgroups measured faster than 128).
-template <bool MFMA>
-__global__ void __launch_bounds__(kFnoBlock) k_conv1x1(ConvArgs a) {
+__device__ inline void conv_epilogue(const ConvArgs& a, size_t o, float y) {
+  if (a.epi == CE_ACCUM) y += a.Y[o];
+  if (a.epi == CE_GELU_GRAD) y *= gelu_grad_f(a.S[o]);
+  a.Y[o] = y;
+  if (a.epi == CE_GELU) a.A[o] = gelu_f(y);
+}
+
+// Y[b][m][p] = sum_k W[m][k] X[b][k][p] + bias[m], then the epilogue, on the
+// matrix cores.  Workgroup: sample blockIdx.y, pixels [64 blockIdx.x, +64);
+// wave w takes a tile of 16 pixels and every 16-row tile of the output channels
+// (64-pixel workgroups measured faster than 128).  KT = Kp / 32, the reduction
+// padded to whole instructions: a compile-time constant, since the index
+// divisions of the two operand fills by a run-time Kp cost more instructions
+// than the products.
+template <int KT>
+__global__ void __launch_bounds__(kFnoBlock) k_conv1x1_mfma(ConvArgs a) {
   extern __shared__ unsigned char smem_raw[];
-  constexpr int PT = MFMA ? kConvPixMfma : kFnoPixTile;
+  constexpr int PT = kConvPixMfma, Kp = 32 * KT, KS = Kp + 8;
   const int b = blockIdx.y, p0 = blockIdx.x * PT;
-  const int Mp = (a.M + 15) & ~15, Kp = (a.K + 31) & ~31;
+  const int Mp = (a.M + 15) & ~15;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const float* Xb = a.X + (size_t)b * a.K * a.P;
-  if (MFMA) {
-    // both operands k-contiguous in LDS, rows padded by 8 elements, so that a
-    // lane's 8 reduction values are one 16-byte read
-    const int KS = Kp + 8;
-    __bf16* Ws = reinterpret_cast<__bf16*>(smem_raw);   // [Mp][KS]
-    __bf16* Xs = Ws + (size_t)Mp * KS;                  // [PT pixels][KS]
-    // weights, then pixels: four global loads in flight per thread before the
-    // converted values go to LDS
-    const int nw = Mp * Kp;
-    for (int i0 = threadIdx.x; i0 < nw; i0 += 4 * kFnoBlock) {
-      float v[4];
+  const float* __restrict__ Xb = a.X + (size_t)b * a.K * a.P;
+  // both operands k-contiguous in LDS, rows padded by 8 elements, so that a
+  // lane's 8 reduction values are one 16-byte read
+  __bf16* Ws = reinterpret_cast<__bf16*>(smem_raw);  // [Mp][KS]
+  __bf16* Xs = Ws + (size_t)Mp * KS;                 // [PT pixels][KS]
+  // pixels (16-byte loads of four pixels of one channel) and the first weights
+  // are in flight together before the converted values go to LDS
+  constexpr int QX = PT / 4, NX = Kp * QX / kFnoBlock;
+  const bool vec = a.P % 4 == 0;
+  f32x4 xv[NX];
+  if (vec) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + u * kFnoBlock, m = i / Kp, k = i - m * Kp;
-        v[u] = 0.f;
-        if (i < nw && m < a.M && k < a.K)
-          v[u] = a.trans ? a.Wt[(size_t)k * a.M + m] : a.Wt[(size_t)m * a.K + k];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + u * kFnoBlock, m = i / Kp, k = i - m * Kp;
-        if (i < nw) Ws[(size_t)m * KS + k] = (__bf16)v[u];
-      }
+    for (int u = 0; u < NX; ++u) {
+      const int i = threadIdx.x + u * kFnoBlock, k = i / QX, px = p0 + 4 * (i % QX);
+      xv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (k < a.K && px < a.P)
+        xv[u] = *reinterpret_cast<const f32x4*>(Xb + (size_t)k * a.P + px);
     }
-    if (a.P % 4 == 0) {
-      // 16-byte loads of four pixels of one channel
-      constexpr int QX = PT / 4;  // 16-byte pieces per channel row
-      const int nx = Kp * QX;
-      for (int i0 = threadIdx.x; i0 < nx; i0 += 4 * kFnoBlock) {
-        f32x4 v[4];
+  }
+  const int nw = Mp * Kp;
+  for (int i0 = threadIdx.x; i0 < nw; i0 += 4 * kFnoBlock) {
+    float v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = i0 + u * kFnoBlock, k = i / QX, px = p0 + 4 * (i % QX);
-          v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-          if (i < nx && k < a.K && px < a.P)
-            v[u] = *reinterpret_cast<const f32x4*>(Xb + (size_t)k * a.P + px);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = i0 + u * kFnoBlock, k = i / QX, q = 4 * (i % QX);
-          if (i < nx) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) Xs[(size_t)(q + e) * KS + k] = (__bf16)v[u][e];
-          }
-        }
-      }
-    } else {
-      for (int i = threadIdx.x; i < Kp * PT; i += blockDim.x) {
-        const int k = i / PT, px = i - k * PT;
-        float v = 0.f;
-        if (k < a.K && p0 + px < a.P) v = Xb[(size_t)k * a.P + p0 + px];
-        Xs[(size_t)px * KS + k] = (__bf16)v;
-      }
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * kFnoBlock, m = i / Kp, k = i % Kp;
+      v[u] = 0.f;
+      if (i < nw && m < a.M && k < a.K) v[u] = a.trans ? a.Wt[k * a.M + m] : a.Wt[m * a.K + k];
     }
-    __syncthreads();
-    const int col = lane & 15, grp = lane >> 4, nkt = Kp / 32;
-    for (int pt = 0; pt < PT / 64; ++pt) {
-      const int px = wave * (PT / 4) + pt * 16 + col;  // this lane's pixel column
-      // B operands of every reduction step (Kp <= 128)
-      bf16x8 bv[4];
 #pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-        if (kt < nkt) bv[kt] = *reinterpret_cast<const bf16x8*>(Xs + (size_t)px * KS + kt * 32 + 8 * grp);
-      for (int mt = 0; mt < Mp / 16; ++mt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const __bf16* wrow = Ws + (size_t)(mt * 16 + col) * KS + 8 * grp;
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * kFnoBlock, m = i / Kp, k = i % Kp;
+      if (i < nw) Ws[m * KS + k] = (__bf16)v[u];
+    }
+  }
+  if (vec) {
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-          if (kt < nkt)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                *reinterpret_cast<const bf16x8*>(wrow + kt * 32), bv[kt], acc, 0, 0, 0);
-        const int p = p0 + px;
+    for (int u = 0; u < NX; ++u) {
+      const int i = threadIdx.x + u * kFnoBlock, k = i / QX, q = 4 * (i % QX);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int m = mt * 16 + 4 * grp + j;
-          if (m < a.M && p < a.P) {
-            const size_t o = ((size_t)b * a.M + m) * a.P + p;
-            float y = acc[j] + (a.bias ? a.bias[m] : 0.f);
-            if (a.epi == CE_ACCUM) y += a.Y[o];
-            if (a.epi == CE_GELU_GRAD) y *= gelu_grad_f(a.S[o]);
-            a.Y[o] = y;
-            if (a.epi == CE_GELU) a.A[o] = gelu_f(y);
-          }
-        }
-      }
+      for (int e = 0; e < 4; ++e) Xs[(q + e) * KS + k] = (__bf16)xv[u][e];
     }
   } else {
-    float* Ws = reinterpret_cast<float*>(smem_raw);     // [M][K]
-    float* Xs = Ws + (size_t)a.M * a.K;                  // [K][64]
-    for (int i = threadIdx.x; i < a.M * a.K; i += blockDim.x) {
-      const int m = i / a.K, k = i - m * a.K;
-      Ws[i] = a.trans ? a.Wt[(size_t)k * a.M + m] : a.Wt[(size_t)m * a.K + k];
+    for (int i = threadIdx.x; i < Kp * PT; i += kFnoBlock) {
+      const int k = i / PT, px = i % PT;
+      float v = 0.f;
+      if (k < a.K && p0 + px < a.P) v = Xb[(size_t)k * a.P + p0 + px];
+      Xs[px * KS + k] = (__bf16)v;
     }
-    for (int i = threadIdx.x; i < a.K * kFnoPixTile; i += blockDim.x) {
-      const int k = i / kFnoPixTile, px = i - k * kFnoPixTile;
-      Xs[i] = (p0 + px < a.P) ? Xb[(size_t)k * a.P + p0 + px] : 0.f;
+  }
+  __syncthreads();
+  const int col = lane & 15, grp = lane >> 4;
+  const int px = wave * 16 + col, p = p0 + px;  // this lane's pixel column
+  bf16x8 bv[KT];                                // B operands of every reduction step
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt)
+    bv[kt] = *reinterpret_cast<const bf16x8*>(Xs + px * KS + kt * 32 + 8 * grp);
+  for (int mt = 0; mt < Mp / 16; ++mt) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const __bf16* wrow = Ws + (mt * 16 + col) * KS + 8 * grp;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          *reinterpret_cast<const bf16x8*>(wrow + kt * 32), bv[kt], acc, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int m = mt * 16 + 4 * grp + j;
+      if (m < a.M && p < a.P)
+        conv_epilogue(a, ((size_t)b * a.M + m) * a.P + p, acc[j] + (a.bias ? a.bias[m] : 0.f));
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < a.M * kFnoPixTile; i += blockDim.x) {
-      const int m = i / kFnoPixTile, px = i - m * kFnoPixTile, p = p0 + px;
-      if (p >= a.P) continue;
-      float y = 0.f;
-      for (int k = 0; k < a.K; ++k) y += Ws[(size_t)m * a.K + k] * Xs[(size_t)k * kFnoPixTile + px];
-      y += a.bias ? a.bias[m] : 0.f;
-      const size_t o = ((size_t)b * a.M + m) * a.P + p;
-      if (a.epi == CE_ACCUM) y += a.Y[o];
-      if (a.epi == CE_GELU_GRAD) y *= gelu_grad_f(a.S[o]);
-      a.Y[o] = y;
-      if (a.epi == CE_GELU) a.A[o] = gelu_f(y);
-    }
+  }
+}
+
+// The same map in FP32 on the vector units (parity checks).
+__global__ void __launch_bounds__(kFnoBlock) k_conv1x1(ConvArgs a) {
+  extern __shared__ unsigned char smem_raw[];
+  constexpr int PT = kFnoPixTile;
+  const int b = blockIdx.y, p0 = blockIdx.x * PT;
+  const float* Xb = a.X + (size_t)b * a.K * a.P;
+  float* Ws = reinterpret_cast<float*>(smem_raw);     // [M][K]
+  float* Xs = Ws + (size_t)a.M * a.K;                  // [K][64]
+  for (int i = threadIdx.x; i < a.M * a.K; i += blockDim.x) {
+    const int m = i / a.K, k = i - m * a.K;
+    Ws[i] = a.trans ? a.Wt[(size_t)k * a.M + m] : a.Wt[(size_t)m * a.K + k];
+  }
+  for (int i = threadIdx.x; i < a.K * PT; i += blockDim.x) {
+    const int k = i / PT, px = i - k * PT;
+    Xs[i] = (p0 + px < a.P) ? Xb[(size_t)k * a.P + p0 + px] : 0.f;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < a.M * PT; i += blockDim.x) {
+    const int m = i / PT, px = i - m * PT, p = p0 + px;
+    if (p >= a.P) continue;
+    float y = 0.f;
+    for (int k = 0; k < a.K; ++k) y += Ws[(size_t)m * a.K + k] * Xs[(size_t)k * PT + px];
+    y += a.bias ? a.bias[m] : 0.f;
+    conv_epilogue(a, ((size_t)b * a.M + m) * a.P + p, y);
   }
 }
 
@@ -174,6 +169,7 @@ struct SpecArgs {
   const float* coef;         // [M1] per-kx scale
   const float* add;          // spec_inv: added field (may alias out) or null
   float* act;                // spec_inv: gelu(out) or null
+  const float* zg;           // spec_inv: out is multiplied by gelu'(zg) (reverse pass) or null
   int H, W, M1, J;
 };
 
@@ -251,6 +247,7 @@ __global__ void __launch_bounds__(kFnoBlock) k_spec_inv(SpecArgs a) {
       s += u.re * f.re + u.im * f.im;
     }
     if (add) s += add[i];
+    if (a.zg) s *= gelu_grad_f(a.zg[(size_t)plane * a.H * a.W + i]);
     out[i] = s;
     if (act) act[i] = gelu_f(s);
   }

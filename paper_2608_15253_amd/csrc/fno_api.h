@@ -12,7 +12,7 @@ struct mmx_fno {
   long oP = 0, op = 0, oQ1 = 0, oq1 = 0, oQ2 = 0, oq2 = 0, nparam = 0;
   std::vector<long> oR, oW, ob;
   // tables and activations
-  DevBuf Fx, Fy, cinv, cone, X0, Y1, A1, dh, dA, dV, dV2, dZ, Uh, dUh, dVh, part, lpart, lsum,
+  DevBuf Fx, Fy, img_fwd, img_inv, cinv, cone, X0, Y1, A1, dh, dA, dV, dV2, Uh, dUh, dVh, part, lpart, lsum,
       loss;
   std::vector<DevBuf> V, Z, Vh;
   int batch = 0;  // batch of the cached forward
@@ -27,13 +27,18 @@ mmx_status fno_conv(mmx_fno* f, const float* X, const float* Wt, const float* bi
   ConvArgs a{X, Wt, bias, Y, A, S, M, K, (int)f->P, trans, epi};
   if (f->mfma) {
     const dim3 grid((unsigned)((f->P + kConvPixMfma - 1) / kConvPixMfma), B);
-    const int Mp = (M + 15) & ~15, KS = ((K + 31) & ~31) + 8;
+    const int Mp = (M + 15) & ~15, KT = (K + 31) / 32, KS = 32 * KT + 8;
     const size_t lds = ((size_t)Mp * KS + (size_t)kConvPixMfma * KS) * sizeof(__bf16);
-    k_conv1x1<true><<<grid, kFnoBlock, lds, f->stream>>>(a);
+    switch (KT) {  // K <= 128
+      case 1: k_conv1x1_mfma<1><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+      case 2: k_conv1x1_mfma<2><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+      case 3: k_conv1x1_mfma<3><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+      default: k_conv1x1_mfma<4><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+    }
   } else {
     const dim3 grid((unsigned)((f->P + kFnoPixTile - 1) / kFnoPixTile), B);
     const size_t lds = ((size_t)M * K + (size_t)K * kFnoPixTile) * sizeof(float);
-    k_conv1x1<false><<<grid, kFnoBlock, lds, f->stream>>>(a);
+    k_conv1x1<<<grid, kFnoBlock, lds, f->stream>>>(a);
   }
   HIP_TRY(hipGetLastError());
   return MMX_OK;
@@ -94,20 +99,38 @@ mmx_status fno_dw(mmx_fno* f, const float* dY, const float* X, int M, int K, int
   return MMX_OK;
 }
 
-// the matrix-core transforms take up to 16 x-modes and 32 y-modes
+// the matrix-core transforms take up to 16 x-modes and 32 y-modes, and tables
+// of up to 64 KB
 bool spec_mfma_fits(const mmx_fno* f, size_t lds_bytes) {
   return f->M1 <= 16 && f->J <= 32 && lds_bytes <= 65536;
+}
+bool spec_fwd_fits(const mmx_fno* f) {
+  return spec_mfma_fits(f, spec_fwd_img_floats(f->H, f->W) * sizeof(float));
+}
+bool spec_inv_fits(const mmx_fno* f) {
+  return spec_mfma_fits(f, spec_inv_lds_floats(f->H, f->W, f->J) * sizeof(float));
+}
+
+// workgroups of a transform over `planes` planes: as many as the chip holds at
+// once (256 CUs of 160 KB LDS), each taking its share of the planes, so that
+// the tables are loaded once per workgroup and not once per plane (1024
+// planes of 128 x 128: 55 KB of tables against 64 KB of data each)
+unsigned spec_groups(int planes, size_t lds_bytes, int split) {
+  const size_t per_cu = std::max<size_t>(1, std::min<size_t>(8, 160 * 1024 / (lds_bytes + 512)));
+  return (unsigned)std::min<size_t>(planes, std::max<size_t>(1, 256 * per_cu / split));
 }
 
 mmx_status fno_spec_fwd(mmx_fno* f, const float* in, float* out, const float* coef, int planes) {
   SpecArgs a{in, out, f->Fx.as<cpx<float>>(), f->Fy.as<cpx<float>>(), coef, nullptr, nullptr,
-             f->H, f->W, f->M1, f->J};
-  const size_t mlds = (size_t)spec_fwd_lds_floats(f->H, f->W) * sizeof(float);
-  if (spec_mfma_fits(f, mlds)) {
+             nullptr, f->H, f->W, f->M1, f->J};
+  if (spec_fwd_fits(f)) {
+    const size_t mlds = (size_t)spec_fwd_lds_floats(f->H, f->W) * sizeof(float);
+    const unsigned grid = spec_groups(planes, mlds, 1);
+    const float* img = f->img_fwd.as<float>();
     if (f->W % 4 == 0)
-      k_spec_fwd_mfma<true><<<planes, kFnoBlock, mlds, f->stream>>>(a);
+      k_spec_fwd_mfma<true><<<grid, kFnoBlock, mlds, f->stream>>>(a, img, planes);
     else
-      k_spec_fwd_mfma<false><<<planes, kFnoBlock, mlds, f->stream>>>(a);
+      k_spec_fwd_mfma<false><<<grid, kFnoBlock, mlds, f->stream>>>(a, img, planes);
   } else {
     const size_t lds = ((size_t)f->M1 * f->W + (size_t)f->J * f->H + (size_t)f->H * f->M1) *
                        sizeof(cpx<float>);
@@ -118,14 +141,15 @@ mmx_status fno_spec_fwd(mmx_fno* f, const float* in, float* out, const float* co
 }
 
 mmx_status fno_spec_inv(mmx_fno* f, const float* in, float* out, const float* coef,
-                        const float* add, float* act, int planes) {
-  SpecArgs a{in, out, f->Fx.as<cpx<float>>(), f->Fy.as<cpx<float>>(), coef, add, act,
+                        const float* add, float* act, int planes, const float* zg = nullptr) {
+  SpecArgs a{in, out, f->Fx.as<cpx<float>>(), f->Fy.as<cpx<float>>(), coef, add, act, zg,
              f->H, f->W, f->M1, f->J};
-  const size_t mlds = (size_t)spec_inv_lds_floats(f->H, f->W, f->J) * sizeof(float);
-  if (spec_mfma_fits(f, mlds)) {
+  if (spec_inv_fits(f)) {
+    const size_t mlds = (size_t)spec_inv_lds_floats(f->H, f->W, f->J) * sizeof(float);
     // two workgroups per plane once each wave still has a y tile
     const int split = ((f->H + 15) / 16 >= 8) ? 2 : 1;
-    k_spec_inv_mfma<<<dim3(planes, split), kFnoBlock, mlds, f->stream>>>(a);
+    const dim3 grid(spec_groups(planes, mlds, split), split);
+    k_spec_inv_mfma<<<grid, kFnoBlock, mlds, f->stream>>>(a, f->img_inv.as<float>(), planes);
   } else {
     const size_t lds = ((size_t)f->M1 * f->W + (size_t)f->J * f->H + (size_t)f->M1 * f->H +
                         (size_t)f->M1 * f->J) * sizeof(cpx<float>);
@@ -143,11 +167,6 @@ mmx_status fno_mix(mmx_fno* f, const float* in, const float* R, float* out, int 
       reinterpret_cast<cpx<float>*>(out), B, f->C, nmode, adjoint);
   HIP_TRY(hipGetLastError());
   return MMX_OK;
-}
-
-__global__ void k_mul_gelu_grad(const float* d, const float* z, float* out, long n) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = d[i] * gelu_grad_f(z[i]);
 }
 
 mmx_status fno_forward_impl(mmx_fno* f, const float* prm, const float* m, float* h, int B) {
@@ -202,15 +221,8 @@ mmx_status fno_backward_impl(mmx_fno* f, const float* prm, const float* h, const
   float* dV2 = f->dV2.as<float>();
   MMX_TRY(fno_conv(f, f->dA.as<float>(), prm + f->oQ1, nullptr, dV, nullptr, nullptr, f->C,
                    f->Cp, 1, CE_STORE, B));
-  const long nC = (long)B * f->C * f->P;
   for (int l = f->L - 1; l >= 0; --l) {
-    const float* dZ = dV;
-    if (l < f->L - 1) {
-      k_mul_gelu_grad<<<(unsigned)((nC + 255) / 256), 256, 0, f->stream>>>(
-          dV, f->Z[l].as<float>(), f->dZ.as<float>(), nC);
-      HIP_TRY(hipGetLastError());
-      dZ = f->dZ.as<float>();
-    }
+    const float* dZ = dV;  // the last layer has no activation; the others' comes below
     const float* Vl = f->V[l].as<float>();
     MMX_TRY(fno_dw(f, dZ, Vl, f->C, f->C, B, g + f->oW[l]));
     MMX_TRY(fno_conv(f, dZ, prm + f->oW[l], nullptr, dV2, nullptr, nullptr, f->C, f->C, 1,
@@ -223,7 +235,9 @@ mmx_status fno_backward_impl(mmx_fno* f, const float* prm, const float* h, const
         reinterpret_cast<cpx<float>*>(g + f->oR[l]), B, f->C, nmode);
     HIP_TRY(hipGetLastError());
     MMX_TRY(fno_mix(f, f->dUh.as<float>(), prm + f->oR[l], f->dVh.as<float>(), B, 1));
-    MMX_TRY(fno_spec_inv(f, f->dVh.as<float>(), dV2, f->cone.as<float>(), dV2, nullptr, B * f->C));
+    // dV of this layer, times gelu' of the layer before (its dZ)
+    MMX_TRY(fno_spec_inv(f, f->dVh.as<float>(), dV2, f->cone.as<float>(), dV2, nullptr, B * f->C,
+                         l > 0 ? f->Z[l - 1].as<float>() : nullptr));
     std::swap(dV, dV2);
   }
   MMX_TRY(fno_dw(f, dV, f->X0.as<float>(), f->C, 5, B, g + f->oP));
@@ -303,6 +317,48 @@ mmx_status mmx_fno_create(int32_t H, int32_t W, int32_t C, int32_t M1, int32_t M
   };
   MMX_TRY(up(f->Fx, fx.data(), fx.size() * sizeof(cpx<float>)));
   MMX_TRY(up(f->Fy, fy.data(), fy.size() * sizeof(cpx<float>)));
+  // LDS images of the matrix-core transforms' tables, padded to whole 1 KB pieces
+  auto image = [&](DevBuf& b, size_t n, auto fill) -> mmx_status {
+    std::vector<float> t((n + 255) / 256 * 256, 0.f);
+    fill(t);
+    return up(b, t.data(), t.size() * sizeof(float));
+  };
+  const int Wp = (W + 15) & ~15, Hp = (H + 15) & ~15, J = f->J;
+  if (spec_fwd_fits(f.get()))
+    MMX_TRY(image(f->img_fwd, spec_fwd_img_floats(H, W), [&](std::vector<float>& t) {
+      float* yr = t.data() + (size_t)Wp * kSpecStride;
+      float* yi = yr + (size_t)Hp * kSpecStride;
+      for (int k = 0; k < M1; ++k)
+        for (int x = 0; x < W; ++x) {
+          t[(size_t)x * kSpecStride + k] = fx[(size_t)k * W + x].re;
+          t[(size_t)x * kSpecStride + 16 + k] = fx[(size_t)k * W + x].im;
+        }
+      for (int j = 0; j < J; ++j)
+        for (int y = 0; y < H; ++y) {
+          yr[(size_t)y * kSpecStride + j] = fy[(size_t)j * H + y].re;
+          yi[(size_t)y * kSpecStride + j] = fy[(size_t)j * H + y].im;
+        }
+    }));
+  if (spec_inv_fits(f.get()))
+    MMX_TRY(image(f->img_inv, spec_inv_img_floats(H, W, J), [&](std::vector<float>& t) {
+      const int Jp = (J + 3) & ~3, SY = ((Hp + 63) & ~63) + 16, SX = Wp + 4;
+      float* yi = t.data() + (size_t)Jp * SY;
+      float* xr = yi + (size_t)Jp * SY;
+      float* xi = xr + (size_t)16 * SX;
+      for (int j = 0; j < J; ++j)
+        for (int y = 0; y < H; ++y) {
+          t[(size_t)j * SY + y] = fy[(size_t)j * H + y].re;
+          yi[(size_t)j * SY + y] = fy[(size_t)j * H + y].im;
+        }
+      for (int k = 0; k < M1; ++k)
+        for (int x = 0; x < W; ++x) {
+          xr[(size_t)k * SX + x] = fx[(size_t)k * W + x].re;
+          xi[(size_t)k * SX + x] = fx[(size_t)k * W + x].im;
+        }
+    }));
+  // the forward transform's tables and tiles exceed the default 64 KB
+  for (const void* k : {(const void*)&k_spec_fwd_mfma<true>, (const void*)&k_spec_fwd_mfma<false>})
+    HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));
   MMX_TRY(up(f->cinv, ci.data(), M1 * sizeof(float)));
   MMX_TRY(up(f->cone, c1.data(), M1 * sizeof(float)));
   const size_t act = (size_t)batch_max * C * f->P * sizeof(float);
@@ -322,7 +378,6 @@ mmx_status mmx_fno_create(int32_t H, int32_t W, int32_t C, int32_t M1, int32_t M
   HIP_TRY(f->dh.alloc((size_t)batch_max * 3 * f->P * sizeof(float)));
   HIP_TRY(f->dV.alloc(act));
   HIP_TRY(f->dV2.alloc(act));
-  HIP_TRY(f->dZ.alloc(act));
   HIP_TRY(f->Uh.alloc(spec));
   HIP_TRY(f->dUh.alloc(spec));
   HIP_TRY(f->dVh.alloc(spec));

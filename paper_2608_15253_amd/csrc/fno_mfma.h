@@ -23,19 +23,24 @@ __device__ inline f32x4 mma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// LDS table fill by a 256-thread workgroup: element i = tid + 256 u, four
-// global loads in flight per thread before the stores
-template <typename Load, typename Store>
-__device__ inline void stage_table(int n, int tid, Load load, Store store) {
-  for (int i0 = tid; i0 < n; i0 += 4 * 256) {
-    cpx<float> v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (i0 + 256 * u < n) v[u] = load(i0 + 256 * u);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (i0 + 256 * u < n) store(i0 + 256 * u, v[u]);
+// Copies n16 pieces of 16 bytes from global memory into LDS, straight from the
+// memory pipe (no registers, no index arithmetic): the transform tables are
+// kept in global memory as images of their LDS layout.  Filled element by
+// element from the plain tables, with two divisions each, they took as many
+// instructions as the transform of a plane.  Whole workgroup of 256 threads;
+// complete after s_waitcnt vmcnt(0) and a barrier (image_ready).
+__device__ inline void image_copy(float* lds, const float* __restrict__ img, int n16) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int c = wave * 64; c < n16; c += 256) {
+    if (c + lane < n16)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(img + 4 * (size_t)(c + lane)),
+          (__attribute__((address_space(3))) void*)(lds + 4 * (size_t)c), 16, 0, 0);
   }
+}
+__device__ inline void image_ready() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -167,40 +172,32 @@ __global__ void __launch_bounds__(1024) k_sum_rows(const float* __restrict__ par
 //            rows j, columns kx; the stage-1 tiles are the B operand)
 // Wave w takes the 16-row y tiles w, w + 4, ...; the four waves' stage-2
 // tiles are summed in LDS in wave order.  VEC: 16-byte row loads (W % 4 == 0).
+// A workgroup keeps its tables and takes the planes blockIdx.x, + gridDim.x, ...
 constexpr int kSpecStride = 36;  // row stride of the x- and y-tables (floats)
 
-__host__ __device__ inline int spec_fwd_lds_floats(int H, int W) {
+// the table image: Re Fx[kx][x] at [x][kx] and Im at [x][16 + kx], then
+// Re Fy[j][y] at [y][j], then Im
+__host__ __device__ inline int spec_fwd_img_floats(int H, int W) {
   const int Wp = (W + 15) & ~15, Hp = (H + 15) & ~15;
-  const int tables = (Wp + 2 * Hp) * kSpecStride;
-  return tables > 4096 ? tables : 4096;  // the reduction reuses the tables
+  return (Wp + 2 * Hp) * kSpecStride;
+}
+__host__ __device__ inline int spec_fwd_lds_floats(int H, int W) {
+  return spec_fwd_img_floats(H, W) + 4096;  // and the four waves' tiles
 }
 
 template <bool VEC>
-__global__ void __launch_bounds__(256) k_spec_fwd_mfma(SpecArgs a) {
+__global__ void __launch_bounds__(256) k_spec_fwd_mfma(SpecArgs a, const float* __restrict__ img,
+                                                       int planes) {
   extern __shared__ unsigned char smem_raw[];
   const int Wp = (a.W + 15) & ~15, Hp = (a.H + 15) & ~15;
-  float* Gx = reinterpret_cast<float*>(smem_raw);  // [Wp][36]: Re Fx[kx][x] at [x][kx], Im at [x][16 + kx]
-  float* FyR = Gx + (size_t)Wp * kSpecStride;      // [Hp][36]: Re Fy[j][y] at [y][j], j < 32
+  float* Gx = reinterpret_cast<float*>(smem_raw);  // [Wp][36]
+  float* FyR = Gx + (size_t)Wp * kSpecStride;      // [Hp][36]
   float* FyI = FyR + (size_t)Hp * kSpecStride;
-  const int tid = threadIdx.x, plane = blockIdx.x;
-  // table fills: four loads in flight per thread before the LDS stores
-  stage_table(16 * Wp, tid, [&](int i) {
-    const int kx = i / Wp, x = i - kx * Wp;
-    return (kx < a.M1 && x < a.W) ? a.Fx[(size_t)kx * a.W + x] : cpx<float>{0.f, 0.f};
-  }, [&](int i, cpx<float> f) {
-    const int kx = i / Wp, x = i - kx * Wp;
-    Gx[x * kSpecStride + kx] = f.re;
-    Gx[x * kSpecStride + 16 + kx] = f.im;
-  });
-  stage_table(32 * Hp, tid, [&](int i) {
-    const int j = i / Hp, y = i - j * Hp;
-    return (j < a.J && y < a.H) ? a.Fy[(size_t)j * a.H + y] : cpx<float>{0.f, 0.f};
-  }, [&](int i, cpx<float> f) {
-    const int j = i / Hp, y = i - j * Hp;
-    FyR[y * kSpecStride + j] = f.re;
-    FyI[y * kSpecStride + j] = f.im;
-  });
-  __syncthreads();
+  f32x4* red = reinterpret_cast<f32x4*>(FyI + (size_t)Hp * kSpecStride);  // [wave][tile][lane]
+  const int tid = threadIdx.x;
+  image_copy(Gx, img, spec_fwd_img_floats(a.H, a.W) / 4);
+  image_ready();
+  for (int plane = blockIdx.x; plane < planes; plane += gridDim.x) {
   const int lane = tid & 63, w = tid >> 6, r = lane & 15, g = lane >> 4;
   const float* V = a.in + (size_t)plane * a.H * a.W;
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
@@ -251,8 +248,7 @@ __global__ void __launch_bounds__(256) k_spec_fwd_mfma(SpecArgs a) {
       oI1 = mma4(r1, cI[t], oI1);
     }
   }
-  __syncthreads();  // tables no longer read: reuse them for the reduction
-  f32x4* red = reinterpret_cast<f32x4*>(smem_raw);  // [wave][tile][lane]
+  if (plane != (int)blockIdx.x) __syncthreads();  // the last plane's tiles are summed
   red[(w * 4 + 0) * 64 + lane] = oR0;
   red[(w * 4 + 1) * 64 + lane] = oI0;
   red[(w * 4 + 2) * 64 + lane] = oR1;
@@ -271,6 +267,7 @@ __global__ void __launch_bounds__(256) k_spec_fwd_mfma(SpecArgs a) {
       if (j < a.J) out[2 * j + part] = sc * s[t];
     }
   }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -283,13 +280,19 @@ __global__ void __launch_bounds__(256) k_spec_fwd_mfma(SpecArgs a) {
 // then out = U + add (add may alias out) and act = gelu(out).  The plane's
 // y tiles are dealt to the waves of gridDim.y workgroups (wave w of
 // workgroup s: tiles 4 s + w, + 4 gridDim.y, ...), each with all x tiles.
-__host__ __device__ inline int spec_inv_lds_floats(int H, int W, int J) {
+// A workgroup keeps its tables and takes the planes blockIdx.x, + gridDim.x, ...
+// The table image: Re Fy[j][y] at [j][SY], Im, then Re Fx[kx][x] at [kx][SX], Im.
+__host__ __device__ inline int spec_inv_img_floats(int H, int W, int J) {
   const int Wp = (W + 15) & ~15, Hp = (H + 15) & ~15, Jp = (J + 3) & ~3;
   const int SY = ((Hp + 63) & ~63) + 16, SX = Wp + 4;
-  return 2 * Jp * 16 + 2 * Jp * SY + 2 * 16 * SX;
+  return 2 * Jp * SY + 2 * 16 * SX;
+}
+__host__ __device__ inline int spec_inv_lds_floats(int H, int W, int J) {
+  return 2 * ((J + 3) & ~3) * 16 + spec_inv_img_floats(H, W, J);
 }
 
-__global__ void __launch_bounds__(256) k_spec_inv_mfma(SpecArgs a) {
+__global__ void __launch_bounds__(256) k_spec_inv_mfma(SpecArgs a, const float* __restrict__ img,
+                                                       int planes) {
   extern __shared__ unsigned char smem_raw[];
   const int Wp = (a.W + 15) & ~15, Hp = (a.H + 15) & ~15, Jp = (a.J + 3) & ~3;
   const int SY = ((Hp + 63) & ~63) + 16, SX = Wp + 4;
@@ -299,36 +302,24 @@ __global__ void __launch_bounds__(256) k_spec_inv_mfma(SpecArgs a) {
   float* FI = FR + (size_t)Jp * SY;
   float* XR = FI + (size_t)Jp * SY;                // [16][SX]: Re Fx[kx][x]
   float* XI = XR + 16 * SX;
-  const int tid = threadIdx.x, plane = blockIdx.x;
-  const cpx<float>* Uh = reinterpret_cast<const cpx<float>*>(a.in) + (size_t)plane * a.M1 * a.J;
-  stage_table(16 * Jp, tid, [&](int i) {
-    const int kx = i / Jp, j = i - kx * Jp;
-    if (kx >= a.M1 || j >= a.J) return cpx<float>{0.f, 0.f};
-    const float c = a.coef ? a.coef[kx] : 1.f;
-    const cpx<float> u = Uh[(size_t)kx * a.J + j];
-    return cpx<float>{c * u.re, c * u.im};
-  }, [&](int i, cpx<float> u) {
-    const int kx = i / Jp, j = i - kx * Jp;
+  const int tid = threadIdx.x;
+  image_copy(FR, img, spec_inv_img_floats(a.H, a.W, a.J) / 4);
+  for (int plane = blockIdx.x; plane < planes; plane += gridDim.x) {
+  if (plane != (int)blockIdx.x) __syncthreads();  // the last plane's modes are read
+  const cpx<float>* __restrict__ Uh =
+      reinterpret_cast<const cpx<float>*>(a.in) + (size_t)plane * a.M1 * a.J;
+  for (int i = tid; i < 16 * Jp; i += 256) {
+    const int kx = i & 15, j = i >> 4;
+    cpx<float> u = {0.f, 0.f};
+    if (kx < a.M1 && j < a.J) {
+      const float c = a.coef ? a.coef[kx] : 1.f;
+      const cpx<float> q = Uh[kx * a.J + j];
+      u = {c * q.re, c * q.im};
+    }
     UR[j * 16 + kx] = u.re;
     UI[j * 16 + kx] = u.im;
-  });
-  stage_table(Jp * Hp, tid, [&](int i) {
-    const int j = i / Hp, y = i - j * Hp;
-    return (j < a.J && y < a.H) ? a.Fy[(size_t)j * a.H + y] : cpx<float>{0.f, 0.f};
-  }, [&](int i, cpx<float> f) {
-    const int j = i / Hp, y = i - j * Hp;
-    FR[j * SY + y] = f.re;
-    FI[j * SY + y] = f.im;
-  });
-  stage_table(16 * Wp, tid, [&](int i) {
-    const int kx = i / Wp, x = i - kx * Wp;
-    return (kx < a.M1 && x < a.W) ? a.Fx[(size_t)kx * a.W + x] : cpx<float>{0.f, 0.f};
-  }, [&](int i, cpx<float> f) {
-    const int kx = i / Wp, x = i - kx * Wp;
-    XR[kx * SX + x] = f.re;
-    XI[kx * SX + x] = f.im;
-  });
-  __syncthreads();
+  }
+  image_ready();
   const int lane = tid & 63, w = tid >> 6, r = lane & 15, g = lane >> 4;
   const size_t base = (size_t)plane * a.H * a.W;
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
@@ -376,13 +367,15 @@ __global__ void __launch_bounds__(256) k_spec_inv_mfma(SpecArgs a) {
           const int y = ty * 16 + 4 * g + t;
           if (y < a.H && x < a.W) {
             const size_t i = base + (size_t)y * a.W + x;
-            const float v = o[t] + av[q][t];
+            float v = o[t] + av[q][t];
+            if (a.zg) v *= gelu_grad_f(a.zg[i]);
             a.out[i] = v;
             if (a.act) a.act[i] = gelu_f(v);
           }
         }
       }
     }
+  }
   }
 }
 
