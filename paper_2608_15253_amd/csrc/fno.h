@@ -132,6 +132,157 @@ __global__ void __launch_bounds__(kFnoBlock) k_conv1x1_mfma(ConvArgs a) {
   }
 }
 
+// The projection V -> Y1 = Q1 V + q1 -> A1 = gelu(Y1) -> h = Q2 A1 + q2 of 64 pixels
+// (sample blockIdx.y, pixels [64 blockIdx.x, +64)), with the arithmetic and the
+// rounding of two k_conv1x1_mfma maps.  Forward (BACK = false): A1 stays in LDS
+// as the second map's operand, so that the two Cp-channel arrays (2 x 67 MB for 8
+// films of 128 x 128 with Cp = 128, written and one read again) never exist: a
+// forward pass of 8 such films takes 223 us, 241 with the two maps apart, and a
+// training step of 32 takes 1988 us (2045).  Bound by the GELU's erf and exp on the
+// vector units (28 us of the forward pass) and, in reverse, by the two writes.  Reverse (BACK = true): Y1 is computed again
+// from V and the forward pass's weights (Q1, q1: workgroup 0 of the forward pass
+// leaves them in `keep`), A1 is written for the weight gradient, and
+// dY1 = (Q2^T dh) gelu'(Y1).
+// KT = C / 32 rounded up; Cp padded to whole instructions, K2 = 32 KT2.
+struct ProjArgs {
+  const float* V;       // [B][C][P]
+  const float* Q1;      // [Cp][C]
+  const float* q1;      // [Cp]
+  const float* Q2;      // [3][Cp]
+  const float* q2;      // [3]
+  float* h;             // [B][3][P] out (forward), dh in (reverse)
+  float* keep;          // forward: receives Q1, q1
+  float* A1;            // reverse: [B][Cp][P]
+  float* dY1;           // reverse: [B][Cp][P]
+  int C, Cp, P, KT2;
+};
+
+template <int KT, bool BACK>
+__global__ void __launch_bounds__(kFnoBlock) k_project_mfma(ProjArgs a) {
+  extern __shared__ unsigned char smem_raw[];
+  constexpr int PT = kConvPixMfma, Kp = 32 * KT, KS = Kp + 8;
+  const int K2 = 32 * a.KT2, KS2 = BACK ? 40 : K2 + 8;
+  const int b = blockIdx.y, p0 = blockIdx.x * PT, C = a.C, Cp = a.Cp, P = a.P;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __bf16* Ws = reinterpret_cast<__bf16*>(smem_raw);  // [K2][KS]: Q1
+  __bf16* Xs = Ws + (size_t)K2 * KS;                 // [PT][KS]: V
+  // forward: [16][KS2] Q2 and [PT][KS2] A1; reverse: [K2][40] Q2^T and [PT][40] dh
+  __bf16* W2 = Xs + (size_t)PT * KS;
+  __bf16* X2 = W2 + (size_t)(BACK ? K2 : 16) * KS2;
+  if (!BACK && blockIdx.x == 0 && b == 0)
+    for (int i = threadIdx.x; i < Cp * C + Cp; i += kFnoBlock)
+      a.keep[i] = i < Cp * C ? a.Q1[i] : a.q1[i - Cp * C];
+  const float* __restrict__ Vb = a.V + (size_t)b * C * P;
+  constexpr int QX = PT / 4, NX = Kp * QX / kFnoBlock;
+  const bool vec = P % 4 == 0;
+  f32x4 xv[NX];
+  if (vec) {
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+      const int i = threadIdx.x + u * kFnoBlock, k = i / QX, px = p0 + 4 * (i % QX);
+      xv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (k < C && px < P) xv[u] = *reinterpret_cast<const f32x4*>(Vb + (size_t)k * P + px);
+    }
+  }
+  const int nw = K2 * Kp;
+  for (int i0 = threadIdx.x; i0 < nw; i0 += 4 * kFnoBlock) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * kFnoBlock, m = i / Kp, k = i % Kp;
+      v[u] = (i < nw && m < Cp && k < C) ? a.Q1[m * C + k] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * kFnoBlock, m = i / Kp, k = i % Kp;
+      if (i < nw) Ws[m * KS + k] = (__bf16)v[u];
+    }
+  }
+  if constexpr (BACK) {
+    const float* __restrict__ dh = a.h + (size_t)b * 3 * P;
+    for (int i = threadIdx.x; i < K2 * 32; i += kFnoBlock) {
+      const int m = i / 32, k = i % 32;
+      W2[m * 40 + k] = (__bf16)((m < Cp && k < 3) ? a.Q2[k * Cp + m] : 0.f);
+    }
+    for (int i = threadIdx.x; i < PT * 32; i += kFnoBlock) {
+      const int k = i / PT, px = i % PT;
+      X2[px * 40 + k] = (__bf16)((k < 3 && p0 + px < P) ? dh[(size_t)k * P + p0 + px] : 0.f);
+    }
+  } else {
+    for (int m = 0; m < 16; ++m)
+      for (int k = threadIdx.x; k < K2; k += kFnoBlock)
+        W2[m * KS2 + k] = (__bf16)((m < 3 && k < Cp) ? a.Q2[m * Cp + k] : 0.f);
+  }
+  if (vec) {
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+      const int i = threadIdx.x + u * kFnoBlock, k = i / QX, q = 4 * (i % QX);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Xs[(q + e) * KS + k] = (__bf16)xv[u][e];
+    }
+  } else {
+    for (int i = threadIdx.x; i < Kp * PT; i += kFnoBlock) {
+      const int k = i / PT, px = i % PT;
+      Xs[px * KS + k] = (__bf16)((k < C && p0 + px < P) ? Vb[(size_t)k * P + p0 + px] : 0.f);
+    }
+  }
+  __syncthreads();
+  const int col = lane & 15, grp = lane >> 4;
+  const int px = wave * 16 + col, p = p0 + px;  // this lane's pixel column
+  bf16x8 bv[KT];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt)
+    bv[kt] = *reinterpret_cast<const bf16x8*>(Xs + px * KS + kt * 32 + 8 * grp);
+  bf16x8 dv;
+  if constexpr (BACK) dv = *reinterpret_cast<const bf16x8*>(X2 + px * 40 + 8 * grp);
+  for (int mt = 0; mt < K2 / 16; ++mt) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const __bf16* wrow = Ws + (mt * 16 + col) * KS + 8 * grp;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          *reinterpret_cast<const bf16x8*>(wrow + kt * 32), bv[kt], acc, 0, 0, 0);
+    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (BACK)
+      d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          *reinterpret_cast<const bf16x8*>(W2 + (mt * 16 + col) * 40 + 8 * grp), dv, d, 0, 0, 0);
+    __bf16 a1[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int m = mt * 16 + 4 * grp + j;
+      float y = 0.f;
+      if (m < Cp) y = acc[j] + a.q1[m];
+      if constexpr (BACK) {
+        if (m < Cp && p < P) {
+          const size_t o = ((size_t)b * Cp + m) * P + p;
+          a.A1[o] = gelu_f(y);
+          a.dY1[o] = d[j] * gelu_grad_f(y);
+        }
+      } else {
+        a1[j] = (__bf16)(m < Cp ? gelu_f(y) : 0.f);
+      }
+    }
+    if constexpr (!BACK) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) X2[px * KS2 + mt * 16 + 4 * grp + j] = a1[j];
+    }
+  }
+  if constexpr (!BACK) {
+    __syncthreads();
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+      if (kt < a.KT2)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            *reinterpret_cast<const bf16x8*>(W2 + col * KS2 + kt * 32 + 8 * grp),
+            *reinterpret_cast<const bf16x8*>(X2 + px * KS2 + kt * 32 + 8 * grp), acc, 0, 0, 0);
+    if (grp == 0 && p < P) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) a.h[((size_t)b * 3 + j) * P + p] = acc[j] + a.q2[j];
+    }
+  }
+}
+
 // The same map in FP32 on the vector units (parity checks).
 __global__ void __launch_bounds__(kFnoBlock) k_conv1x1(ConvArgs a) {
   extern __shared__ unsigned char smem_raw[];

@@ -12,7 +12,7 @@ struct mmx_fno {
   long oP = 0, op = 0, oQ1 = 0, oq1 = 0, oQ2 = 0, oq2 = 0, nparam = 0;
   std::vector<long> oR, oW, ob;
   // tables and activations
-  DevBuf Fx, Fy, img_fwd, img_inv, cinv, cone, X0, Y1, A1, dh, dA, dV, dV2, Uh, dUh, dVh, part, lpart, lsum,
+  DevBuf Fx, Fy, img_fwd, img_inv, cinv, cone, X0, Y1, A1, dh, dA, dV, dV2, keep, Uh, dUh, dVh, part, lpart, lsum,
       loss;
   std::vector<DevBuf> V, Z, Vh;
   int batch = 0;  // batch of the cached forward
@@ -39,6 +39,28 @@ mmx_status fno_conv(mmx_fno* f, const float* X, const float* Wt, const float* bi
     const dim3 grid((unsigned)((f->P + kFnoPixTile - 1) / kFnoPixTile), B);
     const size_t lds = ((size_t)M * K + (size_t)K * kFnoPixTile) * sizeof(float);
     k_conv1x1<<<grid, kFnoBlock, lds, f->stream>>>(a);
+  }
+  HIP_TRY(hipGetLastError());
+  return MMX_OK;
+}
+
+// the fused projection (k_project_mfma), forward or reverse
+size_t project_lds(int C, int Cp, bool back) {
+  const size_t KS = (C + 31) / 32 * 32 + 8, K2 = (Cp + 31) / 32 * 32, PT = kConvPixMfma;
+  const size_t second = back ? (K2 + PT) * 40 : (16 + PT) * (K2 + 8);
+  return ((K2 + PT) * KS + second) * sizeof(__bf16);
+}
+
+template <bool BACK>
+mmx_status fno_project(mmx_fno* f, ProjArgs& a, int B) {
+  a.KT2 = (f->Cp + 31) / 32;
+  const dim3 grid((unsigned)((f->P + kConvPixMfma - 1) / kConvPixMfma), B);
+  const size_t lds = project_lds(f->C, f->Cp, BACK);
+  switch ((f->C + 31) / 32) {
+    case 1: k_project_mfma<1, BACK><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+    case 2: k_project_mfma<2, BACK><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+    case 3: k_project_mfma<3, BACK><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
+    default: k_project_mfma<4, BACK><<<grid, kFnoBlock, lds, f->stream>>>(a); break;
   }
   HIP_TRY(hipGetLastError());
   return MMX_OK;
@@ -188,10 +210,16 @@ mmx_status fno_forward_impl(mmx_fno* f, const float* prm, const float* m, float*
     MMX_TRY(fno_spec_inv(f, f->Uh.as<float>(), Zl, f->cinv.as<float>(), Zl, act, B * f->C));
   }
   const float* VL = f->Z[f->L - 1].as<float>();
-  MMX_TRY(fno_conv(f, VL, prm + f->oQ1, prm + f->oq1, f->Y1.as<float>(), f->A1.as<float>(),
-                   nullptr, f->Cp, f->C, 0, CE_GELU, B));
-  MMX_TRY(fno_conv(f, f->A1.as<float>(), prm + f->oQ2, prm + f->oq2, h, nullptr, nullptr, 3,
-                   f->Cp, 0, CE_STORE, B));
+  if (f->mfma) {
+    ProjArgs a{VL, prm + f->oQ1, prm + f->oq1, prm + f->oQ2, prm + f->oq2, h,
+               f->keep.as<float>(), nullptr, nullptr, f->C, f->Cp, (int)f->P, 0};
+    MMX_TRY(fno_project<false>(f, a, B));
+  } else {
+    MMX_TRY(fno_conv(f, VL, prm + f->oQ1, prm + f->oq1, f->Y1.as<float>(), f->A1.as<float>(),
+                     nullptr, f->Cp, f->C, 0, CE_GELU, B));
+    MMX_TRY(fno_conv(f, f->A1.as<float>(), prm + f->oQ2, prm + f->oq2, h, nullptr, nullptr, 3,
+                     f->Cp, 0, CE_STORE, B));
+  }
   f->batch = B;
   return MMX_OK;
 }
@@ -212,10 +240,17 @@ mmx_status fno_backward_impl(mmx_fno* f, const float* prm, const float* h, const
       h, t, f->lsum.as<double>(), n_per, B, f->dh.as<float>());
   HIP_TRY(hipGetLastError());
   // projection
-  MMX_TRY(fno_dw(f, f->dh.as<float>(), f->A1.as<float>(), 3, f->Cp, B, g + f->oQ2));
-  MMX_TRY(fno_conv(f, f->dh.as<float>(), prm + f->oQ2, nullptr, f->dA.as<float>(), nullptr,
-                   f->Y1.as<float>(), f->Cp, 3, 1, CE_GELU_GRAD, B));
   const float* VL = f->Z[f->L - 1].as<float>();
+  if (f->mfma) {
+    const float* q = f->keep.as<float>();
+    ProjArgs a{VL, q, q + (size_t)f->Cp * f->C, prm + f->oQ2, nullptr, f->dh.as<float>(),
+               nullptr, f->A1.as<float>(), f->dA.as<float>(), f->C, f->Cp, (int)f->P, 0};
+    MMX_TRY(fno_project<true>(f, a, B));
+  } else {
+    MMX_TRY(fno_conv(f, f->dh.as<float>(), prm + f->oQ2, nullptr, f->dA.as<float>(), nullptr,
+                     f->Y1.as<float>(), f->Cp, 3, 1, CE_GELU_GRAD, B));
+  }
+  MMX_TRY(fno_dw(f, f->dh.as<float>(), f->A1.as<float>(), 3, f->Cp, B, g + f->oQ2));
   MMX_TRY(fno_dw(f, f->dA.as<float>(), VL, f->Cp, f->C, B, g + f->oQ1));
   float* dV = f->dV.as<float>();
   float* dV2 = f->dV2.as<float>();
@@ -359,6 +394,10 @@ mmx_status mmx_fno_create(int32_t H, int32_t W, int32_t C, int32_t M1, int32_t M
   // the forward transform's tables and tiles exceed the default 64 KB
   for (const void* k : {(const void*)&k_spec_fwd_mfma<true>, (const void*)&k_spec_fwd_mfma<false>})
     HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));
+  // so does the projection of more than 64 channels
+  for (const void* k : {(const void*)&k_project_mfma<3, false>, (const void*)&k_project_mfma<3, true>,
+                        (const void*)&k_project_mfma<4, false>, (const void*)&k_project_mfma<4, true>})
+    HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));
   MMX_TRY(up(f->cinv, ci.data(), M1 * sizeof(float)));
   MMX_TRY(up(f->cone, c1.data(), M1 * sizeof(float)));
   const size_t act = (size_t)batch_max * C * f->P * sizeof(float);
@@ -372,7 +411,10 @@ mmx_status mmx_fno_create(int32_t H, int32_t W, int32_t C, int32_t M1, int32_t M
     HIP_TRY(f->Vh[l].alloc(spec));
   }
   HIP_TRY(f->X0.alloc((size_t)batch_max * 5 * f->P * sizeof(float)));
-  HIP_TRY(f->Y1.alloc((size_t)batch_max * Cp * f->P * sizeof(float)));
+  if (f->mfma)
+    HIP_TRY(f->keep.alloc(((size_t)Cp * C + Cp) * sizeof(float)));
+  else
+    HIP_TRY(f->Y1.alloc((size_t)batch_max * Cp * f->P * sizeof(float)));
   HIP_TRY(f->A1.alloc((size_t)batch_max * Cp * f->P * sizeof(float)));
   HIP_TRY(f->dA.alloc((size_t)batch_max * Cp * f->P * sizeof(float)));
   HIP_TRY(f->dh.alloc((size_t)batch_max * 3 * f->P * sizeof(float)));
