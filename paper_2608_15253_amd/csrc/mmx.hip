@@ -325,17 +325,11 @@ struct ProfScope {
 // or five passes of a step, and the next step, reread what the one before
 // wrote: a part whose spectrum and states stay in the 256 MB memory-side
 // cache is advanced through a whole captured run before the next part starts.
-// kRunBytes is the working set in flight, parts of half of it on two streams, so
-// that one part's kernels fill the chip while the other's start and drain.
-// Measured per step, films of 64 x 64 (198 KB per replica): 1024 replicas in one part
-// 244.6 us, two on two streams 222, two of 104 MB in turn 267; 2048
-// replicas 600 in one part (its 400 MB miss the cache), 492 in 208 MB parts in turn,
-// 453 in 104 MB parts on two streams, 523 in 130 MB parts; three streams the
-// same, four slower.  512 replicas (101 MB) 134 -> 128 in two; 256 (50 MB) 90 -> 86,
-// but the uneven groups' 13 and 50 MB, split, 1052 -> 1110: hence kSplitBytes.
-constexpr size_t kRunBytes = size_t(208) << 20;
-constexpr size_t kSplitBytes = size_t(64) << 20;  // smaller groups are one part
-constexpr int kRunStreams = 2;
+// Measured per step, films of 64 x 64 (198 KB per replica): 2048 replicas 600 us in one
+// part (its 400 MB miss the cache), 492 in parts of 208 MB; 1024 replicas (203 MB)
+// 245 in one part, 267 in two: a working set within the cache is one part.
+constexpr size_t kRunBytes = size_t(208) << 20;   // of a part
+constexpr size_t kCacheBytes = size_t(256) << 20;
 
 // Captured step sequences kept between calls: Heun / rotation runs of 2^i
 // steps (i < kHeunGraphs) and chunks of RK45 attempts, each valid for the
@@ -381,9 +375,6 @@ struct mmx_ctx {
   // graph replay: library stream, fencing events, step counter, cached graphs
   hipStream_t cap_stream = nullptr;
   hipEvent_t ev_user = nullptr, ev_cap = nullptr;
-  // streams and events that captures fork to and join from (run_concurrent)
-  hipStream_t side[kRunStreams - 1] = {};
-  hipEvent_t ev_fork = nullptr, ev_join[kRunStreams - 1] = {};
   GraphSet heun_graphs, rk_graphs, rk4_graphs;
   uint64_t epoch = 1;  // configuration epoch: advanced by every setter
   Buf stepdev;
@@ -396,11 +387,6 @@ struct mmx_ctx {
     rk4_graphs.clear();
     if (ev_user) (void)hipEventDestroy(ev_user);
     if (ev_cap) (void)hipEventDestroy(ev_cap);
-    if (ev_fork) (void)hipEventDestroy(ev_fork);
-    for (auto e : ev_join)
-      if (e) (void)hipEventDestroy(e);
-    for (auto t : side)
-      if (t) (void)hipStreamDestroy(t);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     if (arena && arena_owned) (void)hipFree(arena);
   }
@@ -1764,39 +1750,7 @@ mmx_status ensure_graph_stream(mmx_ctx* ctx) {
   if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
   if (!ctx->ev_user) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_user, hipEventDisableTiming));
   if (!ctx->ev_cap) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_cap, hipEventDisableTiming));
-  if (!ctx->ev_fork) HIP_TRY(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
-  for (int i = 0; i < kRunStreams - 1; ++i) {
-    if (!ctx->side[i])
-      HIP_TRY(hipStreamCreateWithFlags(&ctx->side[i], hipStreamNonBlocking));
-    if (!ctx->ev_join[i])
-      HIP_TRY(hipEventCreateWithFlags(&ctx->ev_join[i], hipEventDisableTiming));
-  }
   return MMX_OK;
-}
-
-// During a capture on ctx->stream: the chains body(0) .. body(n - 1), which do not
-// depend on each other, on up to kRunStreams streams forked from it and joined
-// to it again.
-template <typename F>
-mmx_status run_concurrent(mmx_ctx* ctx, size_t n, F&& body) {
-  if (n == 1) return body(0);
-  hipStream_t main = ctx->stream;
-  const int ns = (int)std::min<size_t>(n, kRunStreams);
-  HIP_TRY(hipEventRecord(ctx->ev_fork, main));
-  for (int i = 1; i < ns; ++i) HIP_TRY(hipStreamWaitEvent(ctx->side[i - 1], ctx->ev_fork, 0));
-  mmx_status st = MMX_OK;
-  for (size_t p = 0; p < n && st == MMX_OK; ++p) {
-    const int i = (int)(p % ns);
-    ctx->stream = i ? ctx->side[i - 1] : main;
-    st = body(p);
-  }
-  ctx->stream = main;
-  // joined even after an error, so that the capture can end
-  for (int i = 1; i < ns; ++i) {
-    HIP_TRY(hipEventRecord(ctx->ev_join[i - 1], ctx->side[i - 1]));
-    HIP_TRY(hipStreamWaitEvent(main, ctx->ev_join[i - 1], 0));
-  }
-  return st;
 }
 
 // n_steps = a sum of runs of 2^i steps (i < kHeunGraphs, largest first), each
@@ -2014,9 +1968,8 @@ std::vector<ReplicaView> run_parts(const mmx_ctx* ctx, const std::vector<int>& s
     const Group& G = *ctx->groups[gi];
     const size_t per = (size_t)3 * G.nz * G.Sy * G.Kx * cpxb<T>() +
                        (size_t)(rot ? 3 : 2) * 3 * G.N * sizeof(T);
-    const size_t most = std::max<size_t>(1, kRunBytes / kRunStreams / per);
-    int np = (int)(((size_t)G.R + most - 1) / most);
-    if (G.R * per >= kSplitBytes) np = std::max(np, std::min(kRunStreams, G.R));
+    const size_t most = std::max<size_t>(1, kRunBytes / per);
+    const int np = G.R * per <= kCacheBytes ? 1 : (int)(((size_t)G.R + most - 1) / most);
     for (int p = 0; p < np; ++p) {
       const int r0 = (int)((long long)G.R * p / np), r1 = (int)((long long)G.R * (p + 1) / np);
       parts.push_back(replica_view<T>(G, gi, r0, r1 - r0));
@@ -2255,10 +2208,8 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
       if (gs.exec[i]) continue;
       ctx->cur_stepdev = sd;
       const mmx_status st = capture_graph(ctx, [&]() -> mmx_status {
-        MMX_TRY(run_concurrent(ctx, parts.size(), [&](size_t p) -> mmx_status {
-          for (int j = 0; j < (1 << i); ++j) MMX_TRY(one_step(parts[p], (uint64_t)j));
-          return MMX_OK;
-        }));
+        for (ReplicaView& v : parts)
+          for (int j = 0; j < (1 << i); ++j) MMX_TRY(one_step(v, (uint64_t)j));
         k_inc_u64<<<1, 1, 0, ctx->stream>>>(sd, 1ull << i);
         HIP_TRY(hipGetLastError());
         return MMX_OK;
@@ -3170,6 +3121,7 @@ mmx_status mmx_bind(mmx_ctx* ctx, void* ws, size_t bytes, void* stream) {
   if (ctx->cap_stream) HIP_TRY(hipStreamSynchronize(ctx->cap_stream));
   ctx->heun_graphs.clear();
   ctx->rk_graphs.clear();
+  ctx->rk4_graphs.clear();
   ctx->epoch++;
   void* dst = ws;
   bool owned = false;

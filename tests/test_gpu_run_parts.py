@@ -1,5 +1,5 @@
 """Heun and rotation runs whose replicas are split into parts (working sets
-beyond the memory-side cache, and the two-part split from 64 MB on): every
+beyond the memory-side cache): every
 replica bit for bit as in a context of few replicas, which is one part, with
 switching times and through retire/refill; several groups, one of them split.
 """
@@ -30,8 +30,9 @@ def _start(case):
     return m.astype(np.float32).astype(np.float64)
 
 
-# 64 x 64: 198 KB of spectrum and states per replica in FP32, so 2, 2, 3 parts
-@pytest.mark.parametrize("R", [330, 1024, 1100])
+# 64 x 64: 198 KB of spectrum and states per replica in FP32 (247 KB with the
+# rotation), so 1, 2 and 3 parts
+@pytest.mark.parametrize("R", [1024, 1400, 2300])
 @pytest.mark.parametrize("rot", [False, True], ids=["heun", "rotation"])
 def test_parts_equal_single_contexts(R, rot):
     import paper_2608_15253_amd as mmx
@@ -60,10 +61,10 @@ def test_parts_equal_single_contexts(R, rot):
 
 def test_parts_with_refill():
     import paper_2608_15253_amd as mmx
-    R, cap = 340, 4
+    R, cap = 1200, 4
     case = _case((64, 64, 1), R)
     m0 = _start(case)
-    few = [0, 3, 169, 170, 171, 339]
+    few = [0, 3, 599, 600, 601, 1199]
 
     def run(c, start):
         ctx = open_ctx(c, mmx.MMX_F32)
@@ -85,7 +86,7 @@ def test_parts_with_refill():
 
 def test_parts_of_several_groups():
     import paper_2608_15253_amd as mmx
-    groups = [_case((32, 32, 1), 24, 5), _case((64, 64, 1), 340, 6), _case((16, 12, 1), 9, 7)]
+    groups = [_case((32, 32, 1), 24, 5), _case((64, 64, 1), 1400, 6), _case((16, 12, 1), 9, 7)]
     m0 = [_start(c) for c in groups]
 
     def run(cs, starts):
