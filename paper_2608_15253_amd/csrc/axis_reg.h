@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(64) k_ypass_reg(YArgs<T> a) {
     for (int s = 0; s < S2; ++s)
 #pragma unroll
       for (int b = 0; b < N1; ++b)
-        v[s][b] = (b < NB) ? atl((unsigned)(q + N1 * s + N2 * b)) : cpx<T>{0, 0};
+        if (b < NB) v[s][b] = atl((unsigned)(q + N1 * s + N2 * b));
   } else {
 #pragma unroll
     for (int d = 0; d < N2; ++d) X[d] = atl((unsigned)(q + N1 * d));
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(64) k_ypass_reg(YArgs<T> a) {
 #pragma unroll
     for (int s = 0; s < S2; ++s) {
       const int av = q + N1 * s;
-      dft_reg<T, false, N1>(v[s]);
+      dft_reg<T, false, N1, PRUNE>(v[s]);
       Ew[av] = v[s][0];
 #pragma unroll
       for (int cc = 1; cc < N1; ++cc) Ew[cc * STR + av] = cmul(v[s][cc], tw[av * cc]);
@@ -170,7 +170,7 @@ __global__ void __launch_bounds__(64) k_zline_reg(YArgs<T> a) {
     for (int s = 0; s < S2; ++s)
 #pragma unroll
       for (int b = 0; b < N1; ++b)
-        v[s][b] = (b < NB) ? atl(c, (unsigned)(q + N1 * s + N2 * b)) : cpx<T>{0, 0};
+        if (b < NB) v[s][b] = atl(c, (unsigned)(q + N1 * s + N2 * b));
   };
   load(va, 0);
 #pragma unroll
@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(64) k_zline_reg(YArgs<T> a) {
 #pragma unroll
     for (int s = 0; s < S2; ++s) {
       const int av = q + N1 * s;
-      dft_reg<T, false, N1>(v[s]);
+      dft_reg<T, false, N1, PRUNE>(v[s]);
       Ew[av] = v[s][0];
 #pragma unroll
       for (int cc = 1; cc < N1; ++cc) Ew[cc * STR + av] = cmul(v[s][cc], tw[av * cc]);
@@ -224,19 +224,21 @@ __global__ void __launch_bounds__(64) k_zline_reg(YArgs<T> a) {
   for (int c = 0; c < 3; ++c) dft_reg<T, false, N2>(X[c]);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tensor entries are in LDS
   wave_sync();
-  if (live) {
-    // lane q holds kz = q + N1 d of all three components: the product is local
-    const T sy = ylo ? T(1) : T(-1);
+  // lane q holds kz = q + N1 d of all three components: the product is local.
+  // Not under `live`: one block with the transforms around it, whose reads the
+  // compiler then issues together (136 registers and three waves per SIMD for
+  // 83 and five), 84 -> 78 us for 256 x 256 x 32
+  // Rows kz <= n/2 (known from d but for the middle one) hold their own
+  // entries, the others those of n - kz
+  const T sy = ylo ? T(1) : T(-1);
 #pragma unroll
-    for (int d = 0; d < N2; ++d) {
-      const int kz = q + N1 * d;
-      const bool zlo = 2 * kz <= n;
-      const int tz = zlo ? kz : n - kz;
-      const T sz = zlo ? T(1) : T(-1);
-      const float4 e0 = Tl[2 * (tz * NC + wc)], e1 = Tl[2 * (tz * NC + wc) + 1];
-      const T ev[6] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y};
-      tensor_apply(ev, 0, sy, sz, sy * sz, true, X[0][d], X[1][d], X[2][d]);
-    }
+  for (int d = 0; d < N2; ++d) {
+    const int kz = q + N1 * d, tz = d < N2 / 2 ? kz : n - kz;
+    const bool odd = d > N2 / 2 || (d == N2 / 2 && q > 0);
+    const T sz = odd ? T(-1) : T(1);
+    const float4 e0 = Tl[2 * (tz * NC + wc)], e1 = Tl[2 * (tz * NC + wc) + 1];
+    const T ev[6] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y};
+    tensor_apply(ev, 0, sy, sz, sy * sz, true, X[0][d], X[1][d], X[2][d]);
   }
   wave_sync();  // the inverse transposes overwrite E
 #pragma unroll

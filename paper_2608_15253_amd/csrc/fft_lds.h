@@ -41,9 +41,12 @@ struct Dft {
   static __device__ inline cpx<T> rot(cpx<T> a) {
     return INV ? cpx<T>{-a.im, a.re} : cpx<T>{a.im, -a.re};
   }
+  // H (r4, r8, r16): the upper half of the inputs is zero and not read (a
+  // sum with a zero is an instruction otherwise: -0 + 0 is not -0)
+  template <bool H = false>
   static __device__ inline void r4(cpx<T>* v) {
-    cpx<T> s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
-    cpx<T> s13 = cadd(v[1], v[3]), d13 = rot(csub(v[1], v[3]));
+    cpx<T> s02 = H ? v[0] : cadd(v[0], v[2]), d02 = H ? v[0] : csub(v[0], v[2]);
+    cpx<T> s13 = H ? v[1] : cadd(v[1], v[3]), d13 = rot(H ? v[1] : csub(v[1], v[3]));
     v[0] = cadd(s02, s13);
     v[2] = csub(s02, s13);
     v[1] = cadd(d02, d13);
@@ -81,14 +84,15 @@ struct Dft {
     v[2] = cadd(m2, n2);
     v[3] = csub(m2, n2);
   }
+  template <bool H = false>
   static __device__ inline void r8(cpx<T>* v) {
     const T h = T(0.70710678118654752440);
     // radix-2 first stage: pairs (k, k+4)
     cpx<T> a[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      a[k] = cadd(v[k], v[k + 4]);
-      a[k + 4] = csub(v[k], v[k + 4]);
+      a[k] = H ? v[k] : cadd(v[k], v[k + 4]);
+      a[k + 4] = H ? v[k] : csub(v[k], v[k + 4]);
     }
     // twiddles w8^k on the odd half (w8 = exp(-+ i pi / 4))
     {
@@ -201,6 +205,7 @@ struct Dft {
   }
   // 16-point DFT as 4 x 4: DFT4 over n1 of x[4 n1 + n2], twiddle w16^(n2 k1),
   // DFT4 over n2; output index k1 + 4 k2.
+  template <bool H = false>
   static __device__ inline void r16(cpx<T>* v) {
     const T c1 = T(0.92387953251128675613), s1 = T(0.38268343236508977173);
     const T h = T(0.70710678118654752440);
@@ -211,7 +216,7 @@ struct Dft {
 #pragma unroll
     for (int n2 = 0; n2 < 4; ++n2) {
       cpx<T> t[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
-      r4(t);
+      r4<H>(t);
 #pragma unroll
       for (int k1 = 0; k1 < 4; ++k1) {
         const int j = n2 * k1;

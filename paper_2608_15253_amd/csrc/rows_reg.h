@@ -11,8 +11,8 @@
 // lane q takes the N1-point DFTs over b for a = q, q + N1, ... in registers,
 // multiplies by w^(+-a c), the values are transposed through LDS so that lane
 // c holds all a, and an N2-point DFT over a leaves lane c the outputs
-// c + N1 d.  Each spectrum row is read once in coalesced order and paired
-// (S[k] with S[hx - k]) through LDS for the complex-to-real combination.  The
+// c + N1 d.  Each spectrum row is read once, as pairs S[k], S[hx - k] for the
+// complex-to-real combination (rising and falling runs of N1 columns).  The
 // inverse transform's output (the demag field of the row) is staged in LDS,
 // the lanes take the row's cells in coalesced order (x = q + N1 j) and
 // overwrite each cell's field with its new state, which then leaves for HBM
@@ -22,6 +22,10 @@
 // instead of once per radix pass.
 // The cell arithmetic is the one of k_fields; only the butterfly order of
 // the transforms differs.
+// Bound by its bytes (4.5 TB/s, the rate of a large copy) with the vector units
+// two thirds busy: sums of a pair computed once and the zero half of an open
+// row left out took 11 % of the instructions and, for 512 films of 64 x 64, 43.0 -> 39.2 us
+// (predictor) and 46.9 -> 44.3 (corrector).
 #pragma once
 #include "common.h"
 #include "fft_lds.h"
@@ -49,7 +53,8 @@ struct RowSplit {
 // x[q + N1 s + N2 b] (s < S2 with q + N1 s < N2, b < N1); out, v[d] =
 // X[q + N1 d] (d < N2).  E: N1 (N2 + 1) LDS slots of this line (one-wave
 // workgroup, wavefront-scope synchronisation).
-template <typename T, int N1, int N2, bool INV, int NV>
+// HALF: the inputs b >= N1 / 2 (the second half of the line) are zero, unread.
+template <typename T, int N1, int N2, bool INV, bool HALF, int NV>
 __device__ inline void line_transform(cpx<T> (&v)[NV], cpx<T>* E, int q,
                                       const cpx<T>* __restrict__ tw) {
   using RS = RowSplit<N1, N2>;
@@ -59,7 +64,7 @@ __device__ inline void line_transform(cpx<T> (&v)[NV], cpx<T>* E, int q,
   for (int s = 0; s < S2; ++s) {
     const int av = q + N1 * s;
     if (!RS::has(q, s)) continue;
-    dft_reg<T, INV, N1>(&v[s * N1]);
+    dft_reg<T, INV, N1, HALF>(&v[s * N1]);
     E[av] = v[s * N1];
 #pragma unroll
     for (int cc = 1; cc < N1; ++cc) {
@@ -74,27 +79,37 @@ __device__ inline void line_transform(cpx<T> (&v)[NV], cpx<T>* E, int q,
   dft_reg<T, INV, N2>(v);
 }
 
-// Real-to-complex split S[kx] = E + conj(W^kx) O of a row whose half-length
-// transform X sits in the lanes as v[c][d] = X[q + N1 d]: lane q stores
-// kx = q + N1 d and (lane 0) kx = hx; the partner X[hx - kx] comes through
-// LDS, one component at a time (hx slots of E).  Followed by no
-// synchronisation: E is reused only after the next one.
+// Real-to-complex split of a row whose half-length transform Z sits in the
+// lanes as v[c][d] = Z[q + N1 d].  With E = (Z[k] + conj Z[hx - k]) / 2, O =
+// (Z[k] - conj Z[hx - k]) / 2 and t = -i w^k O the columns k and hx - k are
+// S[k] = E + t and S[hx - k] = conj(E - t): one sum, difference and product
+// serve both (12 operations for the pair, 28 for the two apart).  Lane q takes
+// the pairs of two adjacent k < hx / 2, lane 0 also k = hx / 2, which is its own
+// partner.  Z comes through LDS, one component at a time (hx slots of E).
+// Followed by no synchronisation: E is reused only after the next one.
 template <typename T, int N1, int N2, int NV>
 __device__ inline void rows_store_spectrum(const cpx<T> (&v)[3][NV], cpx<T>* E, int q, bool live,
                                            cpx<T>* __restrict__ Srow, size_t cstride,
                                            const cpx<T>* __restrict__ wpost) {
-  constexpr int hx = N1 * N2;
-  auto split = [&](int kx) -> cpx<T> {
-    const cpx<T> Zk = E[kx == hx ? 0 : kx];
-    cpx<T> Zc = E[kx == 0 ? 0 : hx - kx];
-    Zc.im = -Zc.im;
-    const cpx<T> Ev = {T(0.5) * (Zk.re + Zc.re), T(0.5) * (Zk.im + Zc.im)};
-    const cpx<T> O = {T(0.5) * (Zk.re - Zc.re), T(0.5) * (Zk.im - Zc.im)};
-    const cpx<T> w = wpost[kx];
-    return {Ev.re + (w.re * O.im + w.im * O.re), Ev.im - (w.re * O.re - w.im * O.im)};
+  constexpr int hx = N1 * N2, NP = N2 / 2;  // pairs per lane
+  static_assert(N2 % 4 == 0, "two adjacent pairs at a time");
+  cpx<T> wh[NP];  // w^k / 2 of the lane's pairs
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const cpx<T> w = wpost[2 * q + 2 * N1 * (j / 2) + (j & 1)];
+    wh[j] = {T(0.5) * w.re, T(0.5) * w.im};
+  }
+  auto split = [&](int k, cpx<T> w, cpx<T>& lo, cpx<T>& hi) {
+    const cpx<T> Zk = E[k];
+    const cpx<T> Zp = E[k == 0 ? 0 : hx - k];
+    const cpx<T> Ev = {Zk.re + Zp.re, Zk.im - Zp.im};
+    const cpx<T> O = {Zk.re - Zp.re, Zk.im + Zp.im};
+    const cpx<T> t = {w.re * O.im + w.im * O.re, w.im * O.im - w.re * O.re};
+    lo = {T(0.5) * Ev.re + t.re, T(0.5) * Ev.im + t.im};
+    hi = {T(0.5) * Ev.re - t.re, t.im - T(0.5) * Ev.im};
   };
-  // each lane stores two adjacent columns per instruction (a row's N1 lanes
-  // cover 2 N1 consecutive columns), lane 0 also the last column kx = hx
+  // a row's N1 lanes store 2 N1 consecutive columns per instruction, going up
+  // from column 0 and down from column hx
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     if (c > 0) wave_sync();  // the previous component's reads are done
@@ -103,14 +118,22 @@ __device__ inline void rows_store_spectrum(const cpx<T> (&v)[3][NV], cpx<T>* E, 
     wave_sync();
     if (live) {
 #pragma unroll
-      for (int d = 0; d < N2 / 2; ++d) {
-        const int kx = 2 * q + 2 * N1 * d;
-        const cpx<T> s0 = split(kx), s1 = split(kx + 1);
-        cpx<T>* dst = Srow + c * cstride + kx;
-        dst[0] = s0;
-        dst[1] = s1;
+      for (int d = 0; d < NP / 2; ++d) {
+        const int k = 2 * q + 2 * N1 * d;
+        cpx<T> l0, l1, h0, h1;
+        split(k, wh[2 * d], l0, h0);
+        split(k + 1, wh[2 * d + 1], l1, h1);
+        cpx<T>* dst = Srow + c * cstride + k;
+        dst[0] = l0;
+        dst[1] = l1;
+        dst = Srow + c * cstride + hx - k - 1;
+        dst[0] = h1;
+        dst[1] = h0;
       }
-      if (q == 0) Srow[c * cstride + hx] = split(hx);
+      if (q == 0) {
+        const cpx<T> z = E[hx / 2];
+        Srow[c * cstride + hx / 2] = {z.re, -z.im};
+      }
     }
   }
 }
@@ -159,8 +182,14 @@ __global__ void __launch_bounds__(64) k_rows_fwd(FArgs<T> a) {
         if (SP::has(q, s) && live && x + 1 < a.nx) p.im = mr[c * N + row0 + x + 1];
         v[c][s * N1 + b] = p;
       }
+  // an open row ends at x = nx = hx: the second half of the line is zero
+  if (a.nx <= hx) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) line_transform<T, N1, N2, false>(v[c], E, q, twl);
+    for (int c = 0; c < 3; ++c) line_transform<T, N1, N2, false, true>(v[c], E, q, twl);
+  } else {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) line_transform<T, N1, N2, false, false>(v[c], E, q, twl);
+  }
   rows_store_spectrum<T, N1, N2>(v, E, q, live, Srow, cstride, wpl);
 }
 
@@ -204,8 +233,19 @@ __global__ void __launch_bounds__(64) k_rows_reg(FArgs<T> a) {
   // and the waits for it count exactly: a row past the last reads row 0, and
   // what it computes from it is never stored (every store of the kernel is
   // guarded by `live`, and lanes exchange data only within their row)
-  auto sload = [&](int c, int i) { return Srow[c * cstride + q + N1 * i]; };
-  auto slast_load = [&](int c) { return Srow[c * cstride + hx]; };
+  constexpr int NP = N2 / 2;  // pairs (k, hx - k) per lane, k = q + N1 i < hx / 2
+  struct Spec {
+    cpx<T> lo[NP], hi[NP], mid;  // S[k], S[hx - k], S[hx / 2]
+  };
+  auto sload = [&](Spec& s, int c) {
+    const cpx<T>* row = Srow + c * cstride;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      s.lo[i] = row[q + N1 * i];
+      s.hi[i] = row[hx - q - N1 * i];
+    }
+    s.mid = row[hx / 2];
+  };
   // transform and split tables staged in LDS: their loads go out first and
   // the spectrum loads of the up-front case (step 1) right after them, so the
   // two global latencies overlap
@@ -219,15 +259,10 @@ __global__ void __launch_bounds__(64) k_rows_reg(FArgs<T> a) {
     if (i <= hx) wpv[j] = a.wpost[i];
   }
   constexpr bool kUpFront = N2 < 12;
-  cpx<T> sv[kUpFront ? 3 : 1][N2], slast[kUpFront ? 3 : 1];
+  Spec sv[kUpFront ? 3 : 1];
   if constexpr (kUpFront) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-      for (int i = 0; i < N2; ++i)
-        sv[c][i] = sload(c, i);
-      slast[c] = slast_load(c);
-    }
+    for (int c = 0; c < 3; ++c) sload(sv[c], c);
   }
 #pragma unroll
   for (int j = 0; j < TWL; ++j) {
@@ -237,51 +272,41 @@ __global__ void __launch_bounds__(64) k_rows_reg(FArgs<T> a) {
   }
   wave_sync();
   const cpx<T>* tw = twl;  // exp(-2 pi i k / hx), k < hx
-  // 1. inverse x transform of the demag spectrum: inputs Z[k] at k = q + N1 s
-  //    + N2 b (complex-to-real combination of S[k] and S[hx - k]).  Each
-  //    spectrum row is read once, in coalesced order (columns q + N1 i, lane
-  //    0 also hx; all loads issued up front), and staged in LDS, where each
-  //    lane picks its pairs
+  // 1. inverse x transform of the demag spectrum.  The complex-to-real
+  //    combination takes S[k] and S[hx - k] to Z[k] = E + i O and Z[hx - k] =
+  //    conj(E - i O), E = S[k] + conj S[hx - k], O = (S[k] - conj S[hx - k])
+  //    conj(w^k), so each lane loads whole pairs (k = q + N1 i < hx / 2, rising
+  //    and falling rows of N1 columns, each column read once), forms both
+  //    values from one sum, difference and product (12 operations, 20 apart)
+  //    and leaves them in LDS for the transform's inputs k = q + N1 s + N2 b
   //    Rows of up to 64 points load all three components up front; longer
   //    rows (N2 >= 12) load one component at a time, which keeps their
   //    register count down (16 x 16: 195 -> 170 VGPRs; measured faster there
   //    and slower on the 8 x 8 rows); the up-front loads are issued above
+  const bool open = nx <= hx;  // half of the transform's outputs are cells
   cpx<T> v[3][SP::NV];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    if constexpr (kUpFront) {
+    if constexpr (!kUpFront) sload(sv[0], c);
+    const Spec& sp = sv[kUpFront ? c : 0];
 #pragma unroll
-      for (int i = 0; i < N2; ++i) E[q + N1 * i] = sv[c][i];
-      if (q == 0) E[hx] = slast[c];
-    } else {
-#pragma unroll
-      for (int i = 0; i < N2; ++i)
-        sv[0][i] = sload(c, i);
-      slast[0] = slast_load(c);
-#pragma unroll
-      for (int i = 0; i < N2; ++i) E[q + N1 * i] = sv[0][i];
-      if (q == 0) E[hx] = slast[0];
+    for (int i = 0; i < NP; ++i) {
+      const int k = q + N1 * i;
+      const cpx<T> X = sp.lo[i], P = sp.hi[i];
+      const cpx<T> Ev = {X.re + P.re, X.im - P.im}, D = {X.re - P.re, X.im + P.im};
+      const cpx<T> O = cmulc(D, wpl[k]);
+      E[k] = {Ev.re - O.im, Ev.im + O.re};
+      E[hx - k] = {Ev.re + O.im, O.re - Ev.im};  // k = 0: slot hx, unread
     }
+    if (q == 0) E[hx / 2] = {T(2) * sp.mid.re, T(-2) * sp.mid.im};
     wave_sync();
 #pragma unroll
     for (int s = 0; s < S2; ++s)
 #pragma unroll
-      for (int b = 0; b < N1; ++b) {
-        if (!SP::has(q, s)) {
-          v[c][s * N1 + b] = cpx<T>{0, 0};
-          continue;
-        }
-        const int k = q + N1 * s + N2 * b;
-        const cpx<T> Xk = E[k];
-        cpx<T> Xc = E[hx - k];
-        Xc.im = -Xc.im;
-        const cpx<T> Ev = cadd(Xk, Xc);
-        const cpx<T> D = csub(Xk, Xc);
-        const cpx<T> O = cmulc(D, wpl[k]);  // D * conj(W^k)
-        v[c][s * N1 + b] = live ? cpx<T>{Ev.re - O.im, Ev.im + O.re} : cpx<T>{0, 0};
-      }
+      for (int b = 0; b < N1; ++b)
+        v[c][s * N1 + b] = SP::has(q, s) ? E[q + N1 * s + N2 * b] : cpx<T>{0, 0};
     wave_sync();
-    line_transform<T, N1, N2, true>(v[c], E, q, tw);
+    line_transform<T, N1, N2, true, false>(v[c], E, q, tw);
   }
   // lane q holds z[q + N1 d] = H_demag at cells x = 2 (q + N1 d) + {0, 1};
   // stage the row's field in LDS (cells x < nx; nx is even)
@@ -290,7 +315,7 @@ __global__ void __launch_bounds__(64) k_rows_reg(FArgs<T> a) {
 #pragma unroll
     for (int d = 0; d < N2; ++d) {
       const int x = 2 * (q + N1 * d);
-      if (x < nx) {
+      if (d < NP || !open) {
         Hs[c * nx + x] = v[c][d].re;
         Hs[c * nx + x + 1] = v[c][d].im;
       }
@@ -375,21 +400,28 @@ __global__ void __launch_bounds__(64) k_rows_reg(FArgs<T> a) {
     }
   }
   // 2. forward x transform of the new state, inputs at k = q + N1 s + N2 b
-  //    (zero beyond the last cell)
+  //    (zero, and left out, in the second half of an open row's line)
+  auto state_in = [&](int b0, int b1) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c)
+    for (int c = 0; c < 3; ++c)
 #pragma unroll
-    for (int s = 0; s < S2; ++s)
+      for (int s = 0; s < S2; ++s)
 #pragma unroll
-      for (int b = 0; b < N1; ++b) {
-        const int k = q + N1 * s + N2 * b;
-        v[c][s * N1 + b] = (SP::has(q, s) && 2 * k < nx)
-                               ? cpx<T>{Hs[c * nx + 2 * k], Hs[c * nx + 2 * k + 1]}
-                               : cpx<T>{0, 0};
-      }
-  wave_sync();
+        for (int b = b0; b < b1; ++b) {
+          const int k = SP::has(q, s) ? q + N1 * s + N2 * b : 0;  // slots past a < N2: unused
+          v[c][s * N1 + b] = cpx<T>{Hs[c * nx + 2 * k], Hs[c * nx + 2 * k + 1]};
+        }
+    wave_sync();
+  };
+  if (open) {
+    state_in(0, N1 / 2);
 #pragma unroll
-  for (int c = 0; c < 3; ++c) line_transform<T, N1, N2, false>(v[c], E, q, tw);
+    for (int c = 0; c < 3; ++c) line_transform<T, N1, N2, false, true>(v[c], E, q, tw);
+  } else {
+    state_in(0, N1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) line_transform<T, N1, N2, false, false>(v[c], E, q, tw);
+  }
   // 3. the half spectrum of the new state
   rows_store_spectrum<T, N1, N2>(v, E, q, live, Srow, cstride, wpl);
   if (MODE == FM_HEUN2) {

@@ -22,13 +22,16 @@
 
 namespace mmx {
 
-template <typename T, bool INV, int R>
+// R-point transform in registers; HALF: the upper half of the inputs is zero
+// and not read
+template <typename T, bool INV, int R, bool HALF = false>
 __device__ inline void dft_reg(cpx<T>* v) {
+  static_assert(!HALF || R == 4 || R == 8 || R == 16, "half-zero transform");
   if constexpr (R == 2) Dft<T, INV>::r2(v);
-  if constexpr (R == 4) Dft<T, INV>::r4(v);
-  if constexpr (R == 8) Dft<T, INV>::r8(v);
+  if constexpr (R == 4) Dft<T, INV>::template r4<HALF>(v);
+  if constexpr (R == 8) Dft<T, INV>::template r8<HALF>(v);
   if constexpr (R == 12) Dft<T, INV>::r12(v);
-  if constexpr (R == 16) Dft<T, INV>::r16(v);
+  if constexpr (R == 16) Dft<T, INV>::template r16<HALF>(v);
   if constexpr (R == 24) Dft<T, INV>::r24(v);
   if constexpr (R == 32) Dft<T, INV>::r32(v);
 }
@@ -72,20 +75,16 @@ __global__ void __launch_bounds__(64) k_yconv_reg(YArgs<T> a) {
   // it the wait for those loads) ahead of it.
   cpx<T> va[S2][N1], vb[S2][N1];
   // loads are unconditional (a lane past the last column reads the last
-  // column and drops the value), so that no branch splits a batch of loads
-  // and the waits for them can count exactly
+  // column; what it computes is never stored), so that no branch splits a
+  // batch of loads and the waits for them can count exactly
   const unsigned offl = live ? off0 : (unsigned)q * (unsigned)Kx + (unsigned)(Kx - 1);
   auto load = [&](cpx<T> (&v)[S2][N1], int c) {
 #pragma unroll
     for (int s = 0; s < S2; ++s)
 #pragma unroll
       for (int b = 0; b < N1; ++b) {
-        if (b < NB) {
-          const cpx<T> x = at(offl + (unsigned)c * plane + (unsigned)(N1 * s + N2 * b) * (unsigned)Kx);
-          v[s][b] = live ? x : cpx<T>{0, 0};
-        } else {
-          v[s][b] = cpx<T>{0, 0};
-        }
+        if (b < NB)
+          v[s][b] = at(offl + (unsigned)c * plane + (unsigned)(N1 * s + N2 * b) * (unsigned)Kx);
       }
   };
   // twiddle table exp(-2 pi i k / n) staged in LDS (broadcast reads); its
@@ -110,7 +109,7 @@ __global__ void __launch_bounds__(64) k_yconv_reg(YArgs<T> a) {
 #pragma unroll
     for (int s = 0; s < S2; ++s) {
       const int av = q + N1 * s;
-      dft_reg<T, false, N1>(v[s]);
+      dft_reg<T, false, N1, PRUNE>(v[s]);
       Ew[av] = v[s][0];
 #pragma unroll
       for (int cc = 1; cc < N1; ++cc) Ew[cc * STR + av] = cmul(v[s][cc], tw[(av * cc) & (n - 1)]);
@@ -153,13 +152,13 @@ __global__ void __launch_bounds__(64) k_yconv_reg(YArgs<T> a) {
   if (live) {
 #pragma unroll
     for (int d = 0; d < N2; ++d) {
+      // rows ky = q + N1 d <= n/2 (known from d but for the middle one) hold
+      // their own entries, the others those of n - ky with the odd one negated
       const int ky = q + N1 * d;
-      const bool lo = 2 * ky <= n;
-      const int ty = lo ? ky : n - ky;
-      const T sy = lo ? T(1) : T(-1);
-      const float4 e4 = Tl[ty * NC + wc];
-      const T ev[4] = {e4.x, e4.y, e4.z, e4.w};
-      tensor_apply(ev, 0, sy, T(1), sy, false, X[0][d], X[1][d], X[2][d]);
+      const float4 e4 = Tl[(d < N2 / 2 ? ky : n - ky) * NC + wc];
+      const bool odd = d > N2 / 2 || (d == N2 / 2 && q > 0);
+      const T ev[4] = {e4.x, e4.y, e4.z, odd ? -e4.w : e4.w};
+      tensor_apply(ev, 0, T(1), T(1), T(1), false, X[0][d], X[1][d], X[2][d]);
     }
   }
   wave_sync();  // the inverse transposes overwrite E
