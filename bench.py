@@ -171,8 +171,8 @@ def traffic_summary(fetch_csv, write_csv, cmd, R):
                 return v
         return None
     patterns = [("k_xfwd", r"k_xfwd<|k_rows_fwd<"), ("k_yconv", r"k_yconv"),
-                ("k_fields_heun1", r"k_rows_reg<float, \d+, \d+, 2(, false)*>|k_fields<float, 2>"),
-                ("k_fields_heun2", r"k_rows_reg<float, \d+, \d+, 3(, false)*>|k_fields<float, 3>")]
+                ("k_fields_heun1", r"k_rows_reg<float, \d+, \d+, 2(, false)*>|k_fields<float, 2[,>]"),
+                ("k_fields_heun2", r"k_rows_reg<float, \d+, \d+, 3(, false)*>|k_fields<float, 3[,>]")]
     for label, pat in patterns:
         f = find_re(fetch, pat)
         w = find_re(write, pat)

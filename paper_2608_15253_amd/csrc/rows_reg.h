@@ -22,10 +22,10 @@
 // instead of once per radix pass.
 // The cell arithmetic is the one of k_fields; only the butterfly order of
 // the transforms differs.
-// Bound by its bytes (4.5 TB/s, the rate of a large copy) with the vector units
-// two thirds busy: sums of a pair computed once and the zero half of an open
-// row left out took 11 % of the instructions and, for 512 films of 64 x 64, 43.0 -> 39.2 us
-// (predictor) and 46.9 -> 44.3 (corrector).
+// Sums of a pair computed once and the zero half of an open row left out took 12 %
+// of the vector instructions.  One film of 64 x 64: predictor 17.9 -> 16.4 us,
+// corrector 19.8 -> 18.4.  1024 films are bound by their bytes (4.5 TB/s, the rate of a
+// large copy) and stay where they were, 69.5 -> 68.6 and 79.0 -> 78.9.
 #pragma once
 #include "common.h"
 #include "fft_lds.h"
