@@ -35,10 +35,12 @@
  *    MMX_ENONFINITE (and clear it); work already queued is not undone.
  *    mmx_rk45 also returns MMX_ENONFINITE when its step size fell to dt_min
  *    on non-finite error estimates.
- *  - Integrator calls replay captured HIP graphs of their step sequences
- *    (kept between calls with the same arrays and configuration; every setter
- *    call invalidates them), on a library stream ordered after and before the
- *    bound stream by events.
+ *  - mmx_heun, mmx_depondt* and mmx_rk45 replay captured HIP graphs of their
+ *    step sequences (kept between calls with the same arrays and
+ *    configuration; every setter call invalidates them), on a library stream
+ *    ordered after and before the bound stream by events.  A call that has to
+ *    replace them waits on the host for the replays queued before.  mmx_rk4
+ *    launches its kernels on the bound stream and never waits.
  *  - One context per host thread at a time; calls on one context that overlap
  *    from several threads race.
  */

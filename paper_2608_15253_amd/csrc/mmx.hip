@@ -375,7 +375,7 @@ struct mmx_ctx {
   // graph replay: library stream, fencing events, step counter, cached graphs
   hipStream_t cap_stream = nullptr;
   hipEvent_t ev_user = nullptr, ev_cap = nullptr;
-  GraphSet heun_graphs, rk_graphs, rk4_graphs;
+  GraphSet heun_graphs, rk_graphs;
   uint64_t epoch = 1;  // configuration epoch: advanced by every setter
   Buf stepdev;
   const unsigned long long* cur_stepdev = nullptr;
@@ -384,7 +384,6 @@ struct mmx_ctx {
     if (cap_stream) (void)hipStreamSynchronize(cap_stream);
     heun_graphs.clear();
     rk_graphs.clear();
-    rk4_graphs.clear();
     if (ev_user) (void)hipEventDestroy(ev_user);
     if (ev_cap) (void)hipEventDestroy(ev_cap);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
@@ -1753,39 +1752,6 @@ mmx_status ensure_graph_stream(mmx_ctx* ctx) {
   return MMX_OK;
 }
 
-// n_steps = a sum of runs of 2^i steps (i < kHeunGraphs, largest first), each
-// run length captured once by body(2^i) and replayed, on the library's stream
-// between two fences of the caller's.
-template <typename F>
-mmx_status replay_runs(mmx_ctx* ctx, GraphSet& gs, const GraphKey& key, int64_t n_steps, F&& body) {
-  MMX_TRY(ensure_graph_stream(ctx));
-  hipStream_t user = ctx->stream, cs = ctx->cap_stream;
-  if (!gs.valid || !(gs.key == key)) {
-    HIP_TRY(hipStreamSynchronize(cs));
-    gs.clear();
-    gs.exec.assign(kHeunGraphs, nullptr);
-    gs.key = key;
-    gs.valid = true;
-  }
-  std::vector<int> runs;
-  for (int64_t left = n_steps; left > 0;) {
-    int i = kHeunGraphs - 1;
-    while ((int64_t(1) << i) > left) --i;
-    runs.push_back(i);
-    left -= int64_t(1) << i;
-  }
-  for (int i : runs) {
-    if (gs.exec[i]) continue;
-    MMX_TRY(capture_graph(ctx, [&]() -> mmx_status { return body(int64_t(1) << i); }, &gs.exec[i]));
-  }
-  HIP_TRY(hipEventRecord(ctx->ev_user, user));
-  HIP_TRY(hipStreamWaitEvent(cs, ctx->ev_user, 0));
-  for (int i : runs) HIP_TRY(hipGraphLaunch(gs.exec[i], cs));
-  HIP_TRY(hipEventRecord(ctx->ev_cap, cs));
-  HIP_TRY(hipStreamWaitEvent(user, ctx->ev_cap, 0));
-  return MMX_OK;
-}
-
 // ---------------------------------------------------------------------------
 // replica-resident Heun path (2-D films whose half spectrum fits in LDS)
 // ---------------------------------------------------------------------------
@@ -2321,25 +2287,13 @@ mmx_status rk4_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps) {
       MMX_TRY(launch_xfwd<T>(ctx, G, mb + G.off, Combine{}, true, nullptr, dt, nullptr));
     }
   }
-  // a caller that captures its stream (the null stream cannot be) gets plain launches
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (ctx->stream) HIP_TRY(hipStreamIsCapturing(ctx->stream, &cap));
-  if (ctx->prof.on || cap != hipStreamCaptureStatusNone) {
-    for (int64_t i = 0; i < n_steps; ++i) MMX_TRY(one_step());
-    return MMX_OK;
-  }
-  // runs of 2^i captured steps, kept for later calls, as in heun_impl.  Launched
-  // one by one, a kernel of a small grid waits for its arguments, which
-  // are then in host memory (260 ns for each line read, 70 ns in a graph)
-  GraphKey key;
-  key.epoch = ctx->epoch;
-  key.p[0] = m;
-  key.d = dt;
-  return replay_runs(ctx, ctx->rk4_graphs, key, n_steps,
-                     [&](int64_t n) -> mmx_status {
-                       for (int64_t i = 0; i < n; ++i) MMX_TRY(one_step());
-                       return MMX_OK;
-                     });
+  // Plain launches, never captured: the host stays ahead of the device (eight
+  // launches of 2.1 us against 57 us per step on one 128 x 80 film), and a
+  // graph of the same steps is not faster once it exists (60 us per step;
+  // 64 x 64 x 16: 103.6 plain, 106.5 as a graph; 64 films of 64 x 64: 88.9 and
+  // 91.5), while a new array, step size or setter would have to capture again
+  for (int64_t i = 0; i < n_steps; ++i) MMX_TRY(one_step());
+  return MMX_OK;
 }
 
 // max over all replicas and cells of |dm/dt| (synchronous)
@@ -3121,7 +3075,6 @@ mmx_status mmx_bind(mmx_ctx* ctx, void* ws, size_t bytes, void* stream) {
   if (ctx->cap_stream) HIP_TRY(hipStreamSynchronize(ctx->cap_stream));
   ctx->heun_graphs.clear();
   ctx->rk_graphs.clear();
-  ctx->rk4_graphs.clear();
   ctx->epoch++;
   void* dst = ws;
   bool owned = false;
