@@ -2522,42 +2522,69 @@ mmx_status apply_tiles(Group& G, int L, int Wy, int Wz) {
   return MMX_OK;
 }
 
+// A start and a stop event of a timed stretch of a stream.
+struct TimedPair {
+  hipEvent_t a = nullptr, b = nullptr;
+  mmx_status create() {
+    HIP_TRY(hipEventCreate(&a));
+    HIP_TRY(hipEventCreate(&b));
+    return MMX_OK;
+  }
+  // waits for the stop event
+  mmx_status elapsed(float& ms) {
+    HIP_TRY(hipEventSynchronize(b));
+    HIP_TRY(hipEventElapsedTime(&ms, a, b));
+    return MMX_OK;
+  }
+  ~TimedPair() {
+    if (a) (void)hipEventDestroy(a);
+    if (b) (void)hipEventDestroy(b);
+  }
+};
+
 // Time of one field evaluation of group G with its current tiles.  A few
 // evaluations are captured and replayed, the second replay timed: one
 // evaluation of a small grid takes 20 us, as long as its plain launches take
 // the host, which hid differences of a half between tiles (64 x 64 x 16: eight
-// rows per workgroup, the slowest, were chosen).
+// rows per workgroup, the slowest, were chosen).  While the profiler is on,
+// whose events around each launch a capture would swallow, they are launched.
 template <typename T>
 mmx_status time_eval(mmx_ctx* ctx, Group& G, float& ms) {
   MMX_TRY(ensure_graph_stream(ctx));
-  hipStream_t cs = ctx->cap_stream;
   Epilogue ep;
   ep.mode = FM_FIELD;
   ep.out = G.k[0].p;
   const int evals = (size_t)G.R * G.N <= (1u << 19) ? 4 : 1;
-  hipGraphExec_t exec = nullptr;
-  MMX_TRY(capture_graph(ctx, [&]() -> mmx_status {
+  auto eval = [&]() -> mmx_status {
     for (int i = 0; i < evals; ++i)
       MMX_TRY(eval_group<T>(ctx, G, G.ms.as<T>(), Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
                             ctx->terms & ~MMX_THERMAL));
     return MMX_OK;
-  }, &exec));
-  hipEvent_t a = nullptr, b = nullptr;
-  hipError_t e = hipEventCreate(&a);
-  if (e == hipSuccess) e = hipEventCreate(&b);
-  if (e == hipSuccess) e = hipGraphLaunch(exec, cs);  // warms the caches
-  if (e == hipSuccess) e = hipEventRecord(a, cs);
-  if (e == hipSuccess) e = hipGraphLaunch(exec, cs);
-  if (e == hipSuccess) e = hipEventRecord(b, cs);
-  if (e == hipSuccess) e = hipEventSynchronize(b);
-  float t = 0;
-  if (e == hipSuccess) e = hipEventElapsedTime(&t, a, b);
-  if (a) (void)hipEventDestroy(a);
-  if (b) (void)hipEventDestroy(b);
-  (void)hipGraphExecDestroy(exec);
-  HIP_TRY(e);
-  ms = t / evals;
-  return MMX_OK;
+  };
+  const bool plain = ctx->prof.on;
+  hipStream_t s = plain ? ctx->stream : ctx->cap_stream;
+  hipGraphExec_t exec = nullptr;
+  if (!plain) MMX_TRY(capture_graph(ctx, eval, &exec));
+  auto timed = [&]() -> mmx_status {
+    TimedPair ev;
+    MMX_TRY(ev.create());
+    for (int rep = 0; rep < 2; ++rep) {  // the first warms the caches
+      HIP_TRY(hipEventRecord(ev.a, s));
+      if (plain)
+        MMX_TRY(eval());
+      else
+        HIP_TRY(hipGraphLaunch(exec, s));
+      HIP_TRY(hipEventRecord(ev.b, s));
+    }
+    return ev.elapsed(ms);
+  };
+  const mmx_status st = timed();
+  if (exec) {
+    (void)hipStreamSynchronize(s);  // replays of a failed timing may be queued
+    (void)hipGraphExecDestroy(exec);
+  }
+  ms /= evals;
+  return st;
 }
 
 template <typename T>
