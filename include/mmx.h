@@ -412,10 +412,12 @@ mmx_status mmx_topological_charge_noalloc(mmx_ctx* ctx, const void* m, void* Q);
  * Results are identical for every valid choice; only speed changes.
  * mmx_set_tiles rejects sizes outside [1, n_y] / [1, n_x/2 + 1] or beyond the
  * LDS of a workgroup (64 KiB; the fused y-z pass: the device's maximum)
- * (MMX_EINVAL) and synchronises the stream.  mmx_autotune times one field
- * evaluation of every group (after mmx_build_demag) for candidate sizes
- * 1, 2, 4, ..., 32 per tile, keeps the fastest, and synchronises; it
- * overwrites the library's stage buffers, not caller arrays. */
+ * (MMX_EINVAL) and synchronises the stream.  mmx_autotune times field
+ * evaluations of every group (after mmx_build_demag) for candidate sizes
+ * 1, 2, 4, ..., 32 of each tile that the group's kernels take (the FP32
+ * column and pillar kernels of power-of-two lengths take none), keeps the
+ * fastest, and synchronises; it overwrites the library's stage buffers, not
+ * caller arrays. */
 /* Execution path of mmx_heun.  MMX_PATH_STAGED: every field evaluation is
  * three (2-D and few-layer 3-D) or five (other 3-D) launches over all
  * replicas, with the spectrum in

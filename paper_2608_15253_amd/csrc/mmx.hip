@@ -1210,6 +1210,15 @@ bool launch_ypass_reg(const Group& G, const YArgs<T>& y, bool inv, hipStream_t s
   }
 }
 
+// whether launch_zline_reg takes the separate z pass of group G (32-bit
+// offsets within a replica's spectrum)
+template <typename T>
+bool zline_reg_applies(const Group& G) {
+  return std::is_same<T, float>::value && G.is3d &&
+         (G.Pz == 32 || G.Pz == 64 || G.Pz == 128) &&
+         (size_t)3 * G.nz * G.Sy * G.Kx * sizeof(cpx<float>) < (1ull << 31);
+}
+
 // Register z pass with the tensor product of a 3-D FP32 group (Pz = 32, 64
 // or 128, split 4 x 8, 8 x 8, 8 x 16); false: not applicable.
 template <typename T>
@@ -1217,9 +1226,7 @@ bool launch_zline_reg(const Group& G, const YArgs<T>& z, hipStream_t s) {
   if constexpr (!std::is_same<T, float>::value) {
     return false;
   } else {
-    // 32-bit offsets within a replica's spectrum
-    if (!G.is3d || (size_t)3 * G.nz * G.Sy * G.Kx * sizeof(cpx<float>) >= (1ull << 31))
-      return false;
+    if (!zline_reg_applies<T>(G)) return false;
     const bool prune = G.plan_zf.prune != 0;
     auto go = [&](auto k, auto kp, int NC) {
       const dim3 grid((G.Kx + NC - 1) / NC, G.Py, G.R);
@@ -2542,8 +2549,25 @@ struct TimedPair {
   }
 };
 
+// The least of three timed passes on stream s, after one that warms the caches.
+template <typename F>
+mmx_status least_time(hipStream_t s, float& ms, F&& pass) {
+  TimedPair ev;
+  MMX_TRY(ev.create());
+  ms = 1e30f;
+  for (int rep = 0; rep < 4; ++rep) {
+    HIP_TRY(hipEventRecord(ev.a, s));
+    MMX_TRY(pass());
+    HIP_TRY(hipEventRecord(ev.b, s));
+    float t = 0;
+    MMX_TRY(ev.elapsed(t));
+    if (rep > 0) ms = std::min(ms, t);
+  }
+  return MMX_OK;
+}
+
 // Time of one field evaluation of group G with its current tiles.  A few
-// evaluations are captured and replayed, the second replay timed: one
+// evaluations are captured and replayed, the least of three replays taken: one
 // evaluation of a small grid takes 20 us, as long as its plain launches take
 // the host, which hid differences of a half between tiles (64 x 64 x 16: eight
 // rows per workgroup, the slowest, were chosen).  While the profiler is on,
@@ -2565,20 +2589,11 @@ mmx_status time_eval(mmx_ctx* ctx, Group& G, float& ms) {
   hipStream_t s = plain ? ctx->stream : ctx->cap_stream;
   hipGraphExec_t exec = nullptr;
   if (!plain) MMX_TRY(capture_graph(ctx, eval, &exec));
-  auto timed = [&]() -> mmx_status {
-    TimedPair ev;
-    MMX_TRY(ev.create());
-    for (int rep = 0; rep < 2; ++rep) {  // the first warms the caches
-      HIP_TRY(hipEventRecord(ev.a, s));
-      if (plain)
-        MMX_TRY(eval());
-      else
-        HIP_TRY(hipGraphLaunch(exec, s));
-      HIP_TRY(hipEventRecord(ev.b, s));
-    }
-    return ev.elapsed(ms);
-  };
-  const mmx_status st = timed();
+  const mmx_status st = least_time(s, ms, [&]() -> mmx_status {
+    if (plain) return eval();
+    HIP_TRY(hipGraphLaunch(exec, s));
+    return MMX_OK;
+  });
   if (exec) {
     (void)hipStreamSynchronize(s);  // replays of a failed timing may be queued
     (void)hipGraphExecDestroy(exec);
@@ -2604,24 +2619,23 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
       float t;
       MMX_TRY(time_eval<T>(ctx, G, t));
       if (t < bt) { bt = t; bestL = L; }
-      if (t > 1.25f * bt) break;  // larger tiles only get slower from here
     }
     bt = 1e30f;
     for (int W : cand) {
-      if (yz_applies<T>(G)) break;  // the fused y-z pass takes no y tile
+      // the fused y-z pass and the register kernels take no y tile
+      if (yz_applies<T>(G) || yconv_reg_applies<T>(G) || ypass_reg_applies<T>(G)) break;
       if (W > G.Kx || lds_ycols<T>(G.is3d, W, G.Py) > kMaxDynLds) continue;
       MMX_TRY(apply_tiles<T>(G, bestL, W, bestWz));
       float t;
       MMX_TRY(time_eval<T>(ctx, G, t));
       if (t < bt) { bt = t; bestW = W; }
-      if (t > 1.25f * bt) break;
     }
     // few-layer groups: the fused y-z kernel (its column tile tuned) against
     // the separate register y passes around the z pass
     const bool both_yz = yz_applies<T>(G) && ypass_reg_applies<T>(G);
     if (both_yz) G.yz_split = 0;
     float t_fused = 1e30f;
-    if (G.is3d && !zconv_reg_applies<T>(G)) {
+    if (G.is3d && !zconv_reg_applies<T>(G) && (yz_applies<T>(G) || !zline_reg_applies<T>(G))) {
       bt = 1e30f;
       for (int W : cand) {
         if (W > G.Kx || !wz_fits<T>(G, W)) continue;
@@ -2629,7 +2643,6 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
         float t;
         MMX_TRY(time_eval<T>(ctx, G, t));
         if (t < bt) { bt = t; bestWz = W; }
-        if (t > 1.25f * bt) break;
       }
       t_fused = bt;
     }
@@ -2640,38 +2653,29 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
       MMX_TRY(time_eval<T>(ctx, G, t_split));
       G.yz_split = t_split <= t_fused ? 1 : 0;
     }
-    // Heun path: one predictor-corrector step staged (two evaluations) against
-    // one replica-resident step, on a zeroed state (scratch buffer m7)
+    // Heun path: a predictor-corrector step staged (two evaluations) against one
+    // more step of a replica-resident launch, on a zeroed state (scratch buffer
+    // m7).  A launch of one step carries the launch and the table loads of a
+    // whole run of steps: timed so, 256 films of 16 x 16 stayed on the staged path
+    // (36 us per step; 32.5 resident).  It settles the choice where it exceeds
+    // the staged step by more than that (some 20 us).
     G.fused_faster = 0;
     const FusedTiles ft = fused_tiles<T>(ctx, G);
     if (ft.ok) {
       MMX_TRY(ensure_rk_buffers<T>(G));
       HIP_TRY(hipMemsetAsync(G.m7.p, 0, G.m7.bytes, ctx->stream));
-      float staged_ms = 0, fused_ms = 0;
+      float staged_ms = 0, one_ms = 0, four_ms = 0;
       MMX_TRY(time_eval<T>(ctx, G, staged_ms));
-      staged_ms *= 2.0f;
-      hipEvent_t a, b;
-      HIP_TRY(hipEventCreate(&a));
-      HIP_TRY(hipEventCreate(&b));
-      float best = 1e30f;
-      for (int rep = 0; rep < 3; ++rep) {
-        (void)hipEventRecord(a, ctx->stream);
-        mmx_status st = heun_fused<T>(ctx, G, ft, G.m7.as<T>(), 1e-15, 1, 0, nullptr);
-        (void)hipEventRecord(b, ctx->stream);
-        (void)hipEventSynchronize(b);
-        float t = 0;
-        (void)hipEventElapsedTime(&t, a, b);
-        if (st != MMX_OK) {
-          (void)hipEventDestroy(a);
-          (void)hipEventDestroy(b);
-          return st;
-        }
-        if (rep > 0) best = std::min(best, t);
+      auto resident = [&](int steps, float& ms) {
+        return least_time(ctx->stream, ms, [&]() -> mmx_status {
+          return heun_fused<T>(ctx, G, ft, G.m7.as<T>(), 1e-15, steps, 0, nullptr);
+        });
+      };
+      MMX_TRY(resident(1, one_ms));
+      if (one_ms < 2.0f * staged_ms + 0.04f) {
+        MMX_TRY(resident(4, four_ms));
+        G.fused_faster = (four_ms - one_ms) / 3.0f < 2.0f * staged_ms ? 1 : 0;
       }
-      (void)hipEventDestroy(a);
-      (void)hipEventDestroy(b);
-      fused_ms = best;
-      G.fused_faster = fused_ms < staged_ms ? 1 : 0;
     }
   }
   // the timing runs step scratch states (a zero state normalises to NaN):
