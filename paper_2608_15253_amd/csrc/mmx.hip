@@ -211,6 +211,17 @@ struct Buf {
   template <typename U> U* as() const { return reinterpret_cast<U*>(p); }
 };
 
+// Host values of one material parameter, one per cell (empty: uniform).  Copies
+// of a group share them: a Heun call makes one for every part of the replicas.
+struct CellValues {
+  std::shared_ptr<const std::vector<double>> v;
+  bool empty() const { return !v; }
+  double operator[](size_t i) const { return (*v)[i]; }
+  void take(std::vector<double>&& x) {
+    v = x.empty() ? nullptr : std::make_shared<const std::vector<double>>(std::move(x));
+  }
+};
+
 struct Group {
   mmx_group g{};
   int nx = 1, ny = 1, nz = 1, N = 1, R = 1;
@@ -235,10 +246,11 @@ struct Group {
   // per-cell Ms, alpha, Ku, D (mmx_set_material_cells): host values (empty:
   // uniform) and the derived device arrays of FArgs (msr, mgi, gpc, alc, sgc,
   // kuc, dmc)
-  std::vector<double> cMs, calpha, cKu, cD;
+  CellValues cMs, calpha, cKu, cD;
   Buf cell[7];
   int cells_on = 0;
-  std::vector<std::vector<unsigned char>> tables;  // host twiddle tables (tw_x, wpost, tw_y, tw_z, ptw_x, ptw_y, ptw_z)
+  // host twiddle tables (tw_x, wpost, tw_y, tw_z, ptw_x, ptw_y, ptw_z), dropped once uploaded
+  std::vector<std::vector<unsigned char>> tables;
   double stt_p[3] = {0, 0, 1}, stt_P = 0, stt_lambda = 1, stt_eps2 = 0;
   int nblk = 1;       // k_fields workgroups per replica
   int nblk_last = 1;  // workgroups per replica of the last field-kernel launch
@@ -677,6 +689,7 @@ mmx_status arena_init(mmx_ctx* ctx) {
     Buf* dst[7] = {&G.tw_x, &G.wpost, &G.tw_y, &G.tw_z, &G.ptw_x, &G.ptw_y, &G.ptw_z};
     for (int i = 0; i < 7; ++i)
       HIP_TRY(hipMemcpy(dst[i]->p, G.tables[i].data(), G.tables[i].size(), hipMemcpyHostToDevice));
+    G.tables = {};
   }
   return MMX_OK;
 }
@@ -2916,10 +2929,10 @@ mmx_status mmx_set_material_cells(mmx_ctx* ctx, int32_t group, const void* Ms, c
     HIP_TRY(hipStreamSynchronize(ctx->stream));
   }
   G.acell_on = vA.empty() ? 0 : 1;
-  G.cMs = std::move(vMs);
-  G.calpha = std::move(val);
-  G.cKu = std::move(vKu);
-  G.cD = std::move(vD);
+  G.cMs.take(std::move(vMs));
+  G.calpha.take(std::move(val));
+  G.cKu.take(std::move(vKu));
+  G.cD.take(std::move(vD));
   G.cells_on = (!G.cMs.empty() || !G.calpha.empty() || !G.cKu.empty() || !G.cD.empty()) ? 1 : 0;
   return ctx->prec == MMX_F64 ? upload_cells<double>(ctx, G) : upload_cells<float>(ctx, G);
 }
