@@ -337,11 +337,23 @@ struct ProfScope {
 // or five passes of a step, and the next step, reread what the one before
 // wrote: a part whose spectrum and states stay in the 256 MB memory-side
 // cache is advanced through a whole captured run before the next part starts.
-// Measured per step, films of 64 x 64 (198 KB per replica): 2048 replicas 600 us in one
-// part (its 400 MB miss the cache), 492 in parts of 208 MB; 1024 replicas (203 MB)
-// 245 in one part, 267 in two: a working set within the cache is one part.
-constexpr size_t kRunBytes = size_t(208) << 20;   // of a part
-constexpr size_t kCacheBytes = size_t(256) << 20;
+// Against that stands the tail of every pass, which each part pays: just above
+// the cache one part is faster, most of all for blocks, whose passes are more.
+// us per step (parts), the rotation scheme in the second column:
+//   MB   64 x 64         rotation        64 x 64 FP64    512 x 512     96 x 96 x 2    64 x 64 x 4 FP64
+//   270  365, 387(2)     367, 389(2)     667, 693(2)     1164, 1234(2)  526, 562(2)    822, 871(2)
+//   300  454, 416(2)     425, 414(2)     753, 761(2)     1271, 1327(2)  586, 604(2)    916, 965(2)
+//   340  532, 456(2)     479, 449(2)     860, 849(2)     1499, 1517(2)  685, 741(2)   1030, 1084(2)
+//   400  673, 533(2)     592, 499(2)    1014, 987(2)     1775, 1752(2)  938, 824(2)   1231, 1265(2)
+//   500  683(2), 676(3)  698(2), 659(3) 1217(2), 1257(3) 2155(2), 2232(3) 971(2), 1092(3) 1537(2), 1604(3)
+//   900  1360(3), 1168(4) 1271(3), 1108(4) 2259(3), 2196(4) 3943(3), 3897(4) 1760(3), 1789(4) 2752(3), 2810(4)
+// A part of one replica that exceeds the cache gains nothing.
+constexpr size_t part_bytes(bool rot) { return size_t(rot ? 225 : 250) << 20; }  // of a part, to a replica
+// Working sets up to this are one part.  reg: FP32 films whose passes run in
+// registers, at the rate of memory; the others' are bound by their instructions too.
+constexpr size_t split_bytes(bool block, bool f64, bool reg) {
+  return size_t(block ? (f64 ? 450 : 380) : reg ? 285 : 320) << 20;
+}
 
 // Captured step sequences kept between calls: Heun / rotation runs of 2^i
 // steps (i < kHeunGraphs) and chunks of RK45 attempts, each valid for the
@@ -1954,8 +1966,11 @@ std::vector<ReplicaView> run_parts(const mmx_ctx* ctx, const std::vector<int>& s
     const Group& G = *ctx->groups[gi];
     const size_t per = (size_t)3 * G.nz * G.Sy * G.Kx * cpxb<T>() +
                        (size_t)(rot ? 3 : 2) * 3 * G.N * sizeof(T);
-    const size_t most = std::max<size_t>(1, kRunBytes / per);
-    const int np = G.R * per <= kCacheBytes ? 1 : (int)(((size_t)G.R + most - 1) / most);
+    const size_t total = G.R * per;
+    const size_t most = part_bytes(rot);
+    const bool split = total > split_bytes(G.is3d != 0, sizeof(T) == 8, yconv_reg_applies<T>(G)) &&
+                       per <= most;
+    const int np = split ? (int)((total + most - 1) / most) : 1;
     for (int p = 0; p < np; ++p) {
       const int r0 = (int)((long long)G.R * p / np), r1 = (int)((long long)G.R * (p + 1) / np);
       parts.push_back(replica_view<T>(G, gi, r0, r1 - r0));
