@@ -1363,8 +1363,12 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
   const int ncell_blk = L * a.nx;
   const double dt_state = a.dtdev ? *a.dtdev : a.dth;
   const T dt = (T)dt_state;
+  // the Runge-Kutta integrators refuse the thermal term.  With its code, and with
+  // the error weights tested at run time, their FP32 kernels reserved scratch for
+  // spilled scalars, which the runtime allocates at the first launch on a queue
+  constexpr bool kNoise = MODE != FM_RKK && MODE != FM_RK7;
   T sigma = 0;
-  if ((a.terms & T_THERMAL) && a.Trep) {
+  if (kNoise && (a.terms & T_THERMAL) && a.Trep) {
     const double Tr = a.Trep[r];
     // per-cell damping or Ms: sigma_i = sqrt(sigunit T / dt) sqrt(alpha_i Ms / Ms_i)
     if (Tr > 0) sigma = (T)sqrt(((EXT && a.sgc) ? a.sigunit : a.sig2pref) * Tr / a.dt_th);
@@ -1397,7 +1401,7 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
     } else if constexpr (MODE == FM_RK7) {
 #pragma unroll
       for (int j = 0; j < 6; ++j)
-        if (a.e[j] != 0.0) ld3(a.kk[j] + rb, N, cell, pk[j]);
+        if (j != 1) ld3(a.kk[j] + rb, N, cell, pk[j]);  // e[1] = 0 (b2 = b2* = 0)
     } else if constexpr (MODE == FM_HEUN2) {
       ld3(a.m0 + rb, N, cell, pm0);
       if (a.rot) ld3(k1_r, N, cell, pk[0]);
@@ -1440,7 +1444,7 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
     T H[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) H[c] = Hex[c] + Hdm[c] + Han[c] + Hz[c] + Hdd[c];
-    if (sigma != T(0)) {
+    if (kNoise && sigma != T(0)) {
       T eta[3];
       uint32_t gen;
       const uint64_t sn = noise_step(a, r, step_now, gen);
@@ -1523,7 +1527,7 @@ __global__ void __launch_bounds__(kBlock) k_fields(FArgs<T> a) {
         double s = a.e[6] * (double)k[c];
 #pragma unroll
         for (int j = 0; j < 6; ++j)
-          if (a.e[j] != 0.0) s += a.e[j] * (double)pk[j][c];
+          if (j != 1) s += a.e[j] * (double)pk[j][c];
         s *= dt_state;
         d2 += s * s;
       }
