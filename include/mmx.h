@@ -415,8 +415,8 @@ mmx_status mmx_topological_charge_noalloc(mmx_ctx* ctx, const void* m, void* Q);
  * (MMX_EINVAL) and synchronises the stream.  mmx_autotune times field
  * evaluations of every group (after mmx_build_demag) for candidate sizes
  * 1, 2, 4, ..., 32 of each tile that the group's kernels take (the FP32
- * column and pillar kernels of power-of-two lengths take none), keeps the
- * fastest, and synchronises; it overwrites the library's stage buffers, not
+ * column and pillar kernels of power-of-two lengths take none) until two in a
+ * row are well behind, keeps the fastest, and synchronises; it overwrites the library's stage buffers, not
  * caller arrays. */
 /* Execution path of mmx_heun.  MMX_PATH_STAGED: every field evaluation is
  * three (2-D and few-layer 3-D) or five (other 3-D) launches over all

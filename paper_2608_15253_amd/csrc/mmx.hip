@@ -2594,8 +2594,8 @@ mmx_status least_time(hipStream_t s, float& ms, F&& pass) {
   return MMX_OK;
 }
 
-// Time of one field evaluation of group G with its current tiles.  A few
-// evaluations are captured and replayed, the least of three replays taken: one
+// Time of one field evaluation of group G with its current tiles.  One or two
+// are captured and replayed, the least of three replays taken: one
 // evaluation of a small grid takes 20 us, as long as its plain launches take
 // the host, which hid differences of a half between tiles (64 x 64 x 16: eight
 // rows per workgroup, the slowest, were chosen).  While the profiler is on,
@@ -2606,7 +2606,7 @@ mmx_status time_eval(mmx_ctx* ctx, Group& G, float& ms) {
   Epilogue ep;
   ep.mode = FM_FIELD;
   ep.out = G.k[0].p;
-  const int evals = (size_t)G.R * G.N <= (1u << 19) ? 4 : 1;
+  const int evals = (size_t)G.R * G.N <= (1u << 19) ? 2 : 1;
   auto eval = [&]() -> mmx_status {
     for (int i = 0; i < evals; ++i)
       MMX_TRY(eval_group<T>(ctx, G, G.ms.as<T>(), Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
@@ -2640,38 +2640,44 @@ mmx_status autotune_impl(mmx_ctx* ctx) {
     HIP_TRY(hipStreamSynchronize(ctx->stream));  // time_eval runs on the library's stream
     const int cand[] = {1, 2, 4, 8, 16, 32};
     int bestL = G.L, bestW = G.Wy, bestWz = G.Wz;
+    // times the candidates in ascending order and keeps the fastest; two in a
+    // row of 1.25 times its time end the search
+    auto search = [&](int& best, float& bt, auto&& fits, auto&& apply) -> mmx_status {
+      int slow = 0;
+      bt = 1e30f;
+      for (int c : cand) {
+        if (!fits(c)) continue;
+        MMX_TRY(apply(c));
+        float t;
+        MMX_TRY(time_eval<T>(ctx, G, t));
+        if (t < bt) { bt = t; best = c; }
+        slow = t > 1.25f * bt ? slow + 1 : 0;
+        if (slow == 2) break;
+      }
+      return MMX_OK;
+    };
     float bt = 1e30f;
-    for (int L : cand) {
-      if (L > G.ny || lds_x<T>(G, L) > kMaxDynLds || (size_t)L * G.nx > 8 * kBlock) continue;
-      MMX_TRY(apply_tiles<T>(G, L, bestW, bestWz));
-      float t;
-      MMX_TRY(time_eval<T>(ctx, G, t));
-      if (t < bt) { bt = t; bestL = L; }
-    }
-    bt = 1e30f;
-    for (int W : cand) {
-      // the fused y-z pass and the register kernels take no y tile
-      if (yz_applies<T>(G) || yconv_reg_applies<T>(G) || ypass_reg_applies<T>(G)) break;
-      if (W > G.Kx || lds_ycols<T>(G.is3d, W, G.Py) > kMaxDynLds) continue;
-      MMX_TRY(apply_tiles<T>(G, bestL, W, bestWz));
-      float t;
-      MMX_TRY(time_eval<T>(ctx, G, t));
-      if (t < bt) { bt = t; bestW = W; }
-    }
+    MMX_TRY(search(bestL, bt,
+                   [&](int L) {
+                     return L <= G.ny && lds_x<T>(G, L) <= kMaxDynLds &&
+                            (size_t)L * G.nx <= 8 * kBlock;
+                   },
+                   [&](int L) { return apply_tiles<T>(G, L, bestW, bestWz); }));
+    // the fused y-z pass and the register kernels take no y tile
+    if (!yz_applies<T>(G) && !yconv_reg_applies<T>(G) && !ypass_reg_applies<T>(G))
+      MMX_TRY(search(bestW, bt,
+                     [&](int W) {
+                       return W <= G.Kx && lds_ycols<T>(G.is3d, W, G.Py) <= kMaxDynLds;
+                     },
+                     [&](int W) { return apply_tiles<T>(G, bestL, W, bestWz); }));
     // few-layer groups: the fused y-z kernel (its column tile tuned) against
     // the separate register y passes around the z pass
     const bool both_yz = yz_applies<T>(G) && ypass_reg_applies<T>(G);
     if (both_yz) G.yz_split = 0;
     float t_fused = 1e30f;
     if (G.is3d && !zconv_reg_applies<T>(G) && (yz_applies<T>(G) || !zline_reg_applies<T>(G))) {
-      bt = 1e30f;
-      for (int W : cand) {
-        if (W > G.Kx || !wz_fits<T>(G, W)) continue;
-        MMX_TRY(apply_tiles<T>(G, bestL, bestW, W));
-        float t;
-        MMX_TRY(time_eval<T>(ctx, G, t));
-        if (t < bt) { bt = t; bestWz = W; }
-      }
+      MMX_TRY(search(bestWz, bt, [&](int W) { return W <= G.Kx && wz_fits<T>(G, W); },
+                     [&](int W) { return apply_tiles<T>(G, bestL, bestW, W); }));
       t_fused = bt;
     }
     MMX_TRY(apply_tiles<T>(G, bestL, bestW, bestWz));
