@@ -18,7 +18,9 @@
  *    mmx_destroy unless the caller supplies its own with mmx_bind; after
  *    mmx_create no call allocates device memory except mmx_build_demag
  *    (its FP64 tensor staging, freed before it returns) and the network
- *    calls (mmx_fno_*, which own their buffers).
+ *    calls (mmx_fno_*, which own their buffers).  Tests hold this for the
+ *    fixed-step integrators, the observables and mmx_rk45 on films; mmx_rk45
+ *    on ensembles of many replicas is not covered by one.
  *  - Magnetisation layout ("D1", Results "A replica-batched engine" and the
  *    replica-batching figure legend: replica-outermost, component-major,
  *    x-fastest): group g, replica r, component c, cell (x, y, z) lives at
