@@ -1672,8 +1672,9 @@ mmx_status rk45_impl(mmx_ctx* ctx, void* m, double t0, double t_end, double tol,
       MMX_TRY(eval_group<T>(ctx, G, mb + G.off, Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr));
       const double V = G.g.cell[0] * G.g.cell[1] * G.g.cell[2];
       const double cq = -0.5 * kMu0 * G.mat.Ms * V, cz = -kMu0 * G.mat.Ms * V;
-      k_energy_reduce<<<(G.R + 63) / 64, 64, 0, ctx->stream>>>(G.partial.as<double>(), G.nblk, G.R, cq, cz,
-                                                      ctx->Etmp.as<double>() + (size_t)roff * 6);
+      k_energy_reduce<<<sum_grid(G.nblk, G.R), 64, 0, ctx->stream>>>(
+          G.partial.as<double>(), G.nblk, G.R, sum_lanes(G.nblk), cq, cz,
+          ctx->Etmp.as<double>() + (size_t)roff * 6);
       HIP_TRY(hipGetLastError());
       roff += G.R;
     }
@@ -2106,8 +2107,8 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
                             0xFFFFFFFFu, true));
       if (refill) {
         ProfScope ps(ctx->prof, "k_refill", st);
-        k_refill_check<<<(G.R + 63) / 64, 64, 0, st>>>(
-            G.partial.as<double>(), G.nblk_last, G.R, G.N, G.tgen.as<int>(),
+        k_refill_check<<<sum_grid(G.nblk_last, G.R), 64, 0, st>>>(
+            G.partial.as<double>(), G.nblk_last, G.R, sum_lanes(G.nblk_last), G.N, G.tgen.as<int>(),
             G.tstart.as<unsigned long long>(), G.tflag.as<int>(), rf->counts + roff,
             rf->times + (size_t)roff * rf->cap, rf->cap, (unsigned long long)step,
             ctx->cur_stepdev, dt);
@@ -2124,10 +2125,9 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
       }
       if (tsw_d && !folds[gi]) {
         ProfScope ps(ctx->prof, "k_switch_reduce", st);
-        k_switch_reduce<<<(G.R + 63) / 64, 64, 0, st>>>(G.partial.as<double>(), G.nblk_last, G.R,
-                                                         G.N, tsw_d + roff,
-                                                         (unsigned long long)(step + 1),
-                                                         ctx->cur_stepdev, dt);
+        k_switch_reduce<<<sum_grid(G.nblk_last, G.R), 64, 0, st>>>(
+            G.partial.as<double>(), G.nblk_last, G.R, sum_lanes(G.nblk_last), G.N, tsw_d + roff,
+            (unsigned long long)(step + 1), ctx->cur_stepdev, dt);
         HIP_TRY(hipGetLastError());
       }
     }
@@ -2235,10 +2235,9 @@ mmx_status heun_impl(mmx_ctx* ctx, void* m, double dt, int64_t n_steps, uint64_t
     if (!folds[v.gi]) continue;
     const Group& G = v.g;
     ProfScope ps(ctx->prof, "k_switch_reduce", s);
-    k_switch_reduce<<<(G.R + 63) / 64, 64, 0, s>>>(G.partial.as<double>(), G.nblk_last, G.R, G.N,
-                                                   tsw_d + roffs[v.gi] + v.r0,
-                                                   (unsigned long long)(step0 + (uint64_t)n_steps),
-                                                   nullptr, dt);
+    k_switch_reduce<<<sum_grid(G.nblk_last, G.R), 64, 0, s>>>(
+        G.partial.as<double>(), G.nblk_last, G.R, sum_lanes(G.nblk_last), G.N,
+        tsw_d + roffs[v.gi] + v.r0, (unsigned long long)(step0 + (uint64_t)n_steps), nullptr, dt);
     HIP_TRY(hipGetLastError());
   }
   return MMX_OK;
@@ -2425,8 +2424,8 @@ mmx_status energy_impl(mmx_ctx* ctx, const void* m, void* E) {
     MMX_TRY(eval_group<T>(ctx, G, mb + G.off, Combine{}, ep, 0, 1.0, nullptr, 0.0, nullptr,
                           ctx->terms & ~MMX_THERMAL));
     const double V = G.g.cell[0] * G.g.cell[1] * G.g.cell[2];
-    k_energy_reduce<<<(G.R + 63) / 64, 64, 0, ctx->stream>>>(
-        G.partial.as<double>(), G.nblk, G.R, -0.5 * kMu0 * G.mat.Ms * V, -kMu0 * G.mat.Ms * V,
+    k_energy_reduce<<<sum_grid(G.nblk, G.R), 64, 0, ctx->stream>>>(
+        G.partial.as<double>(), G.nblk, G.R, sum_lanes(G.nblk), -0.5 * kMu0 * G.mat.Ms * V, -kMu0 * G.mat.Ms * V,
         Eb + (size_t)roff * 6);
     HIP_TRY(hipGetLastError());
     roff += G.R;

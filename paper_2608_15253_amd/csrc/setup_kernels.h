@@ -276,29 +276,80 @@ __global__ void k_rk_commit(const RkState* st, T* m, const T* m7, T* k1, const T
   }
 }
 
-// per-replica fixed-order sums of workgroup partials; the check's time is
-// step_after dt, step_after = (*stepdev if set) + the given count
-__global__ void k_switch_reduce(const double* partial, int nblk, int R, int N, double* tsw,
-                                unsigned long long step_after, const unsigned long long* stepdev,
-                                double dt) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= R) return;
-  const unsigned long long st = (stepdev ? *stepdev : 0ull) + step_after;
-  switch_check(partial, tsw, nblk, N, r, (double)st * dt);
+// Sums of NV interleaved workgroup partials of replica r, in their order
+// whatever the number of threads: one thread per replica (lanes = 1), or a wave
+// (a workgroup of 64 lanes per replica) that loads a tile of them at once and adds
+// each sum in one lane.  A thread that loads each partial before it adds it takes
+// 0.12 us for one (1024 workgroups of a 128 x 128 x 8 FP64 block: 120 us for the
+// energies, 5 us for the wave); a wave per replica is for many workgroups.
+// Returns whether this lane holds sums (s[v] valid); callers with lanes = 64 have
+// no other use of the workgroup's barrier.
+constexpr int kSumTile = 512;
+template <int NV>
+__device__ inline bool replica_sums(const double* __restrict__ partial, int nblk, int r, int lanes,
+                                    double s[NV]) {
+  const double* p = partial + (size_t)r * nblk * NV;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) s[v] = 0;
+  if (lanes == 1) {
+    for (int b = 0; b < nblk; ++b)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) s[v] += p[(size_t)b * NV + v];
+    return true;
+  }
+  __shared__ double tile[kSumTile * NV], sums[NV];
+  const int t = threadIdx.x;
+  double acc = 0;  // lane v < NV: sum v
+  for (int base = 0; base < nblk; base += kSumTile) {
+    const int n = min(kSumTile, nblk - base);
+    __syncthreads();
+    for (int i = t; i < n * NV; i += 64) tile[i] = p[(size_t)base * NV + i];
+    __syncthreads();
+    if (t < NV)
+      for (int b = 0; b < n; ++b) acc += tile[b * NV + t];
+  }
+  if (t < NV) sums[t] = acc;
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < NV; ++v) s[v] = sums[v];
+  return t == 0;
+}
+// lanes per replica for nblk partials, the grid of 64-thread workgroups for R
+// replicas, and the replica of a thread
+inline int sum_lanes(int nblk) { return nblk >= 32 ? 64 : 1; }
+inline unsigned sum_grid(int nblk, int R) {
+  return sum_lanes(nblk) == 1 ? (unsigned)(R + 63) / 64 : (unsigned)R;
+}
+__device__ inline int sum_replica(int lanes) {
+  return lanes == 1 ? (int)(blockIdx.x * blockDim.x + threadIdx.x) : (int)blockIdx.x;
 }
 
-// Retire/refill bookkeeping after a step (one thread per replica): a replica
-// whose mean m_z is negative ends its trial, records the trial's duration
-// (while fewer than cap are recorded), starts trial g + 1 at the next step and
-// is flagged for a reset to its initial state.
-__global__ void k_refill_check(const double* partial, int nblk, int R, int N, int* tgen,
+// per-replica fixed-order sums of workgroup partials; the check's time is
+// step_after dt, step_after = (*stepdev if set) + the given count
+__global__ void k_switch_reduce(const double* partial, int nblk, int R, int lanes, int N,
+                                double* tsw, unsigned long long step_after,
+                                const unsigned long long* stepdev, double dt) {
+  const int r = sum_replica(lanes);
+  if (r >= R) return;
+  double s[1];
+  if (!replica_sums<1>(partial, nblk, r, lanes, s)) return;
+  const unsigned long long st = (stepdev ? *stepdev : 0ull) + step_after;
+  if (tsw[r] < 0 && s[0] / N < 0) tsw[r] = (double)st * dt;
+}
+
+// Retire/refill bookkeeping after a step: a replica whose mean m_z is
+// negative ends its trial, records the trial's duration (while fewer than cap
+// are recorded), starts trial g + 1 at the next step and is flagged for a
+// reset to its initial state.
+__global__ void k_refill_check(const double* partial, int nblk, int R, int lanes, int N, int* tgen,
                                unsigned long long* tstart, int* flag, int* counts, double* times,
                                int cap, unsigned long long step_host,
                                const unsigned long long* stepdev, double dt) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  const int r = sum_replica(lanes);
   if (r >= R) return;
-  double s = 0;
-  for (int b = 0; b < nblk; ++b) s += partial[(size_t)r * nblk + b];
+  double sum[1];
+  if (!replica_sums<1>(partial, nblk, r, lanes, sum)) return;
+  const double s = sum[0];
   const unsigned long long step = (stepdev ? *stepdev : 0ull) + step_host;
   int f = 0;
   if (s / N < 0) {
@@ -383,13 +434,12 @@ __global__ void k_max_fold(double* part, int n) {
 __global__ void k_set_u64(unsigned long long* p, unsigned long long v) { *p = v; }
 __global__ void k_inc_u64(unsigned long long* p, unsigned long long d) { *p += d; }
 
-__global__ void k_energy_reduce(const double* partial, int nblk, int R, double cq, double cz,
-                                double* E) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void k_energy_reduce(const double* partial, int nblk, int R, int lanes, double cq,
+                                double cz, double* E) {
+  const int r = sum_replica(lanes);
   if (r >= R) return;
-  double s[5] = {0, 0, 0, 0, 0};
-  for (int b = 0; b < nblk; ++b)
-    for (int v = 0; v < 5; ++v) s[v] += partial[((size_t)r * nblk + b) * 5 + v];
+  double s[5];
+  if (!replica_sums<5>(partial, nblk, r, lanes, s)) return;
   double tot = 0;
   for (int v = 0; v < 5; ++v) {
     const double e = (v == 4 ? cz : cq) * s[v];
