@@ -989,6 +989,13 @@ bool launch_rows_reg(mmx_ctx* ctx, Group& G, FArgs<T>& a, int mode) {
 // padded against bank conflicts and indexed by constants (0: the run-time
 // kernels, for every other length and where the padded lines exceed the 64 KB
 // that any tile may use).  lds(ld): bytes with ld slots per line.
+// us per field evaluation of one film, constants for run-time lengths (rows of
+// the given half-length):
+//   points        32            64            128           256
+//   FP32 field    13.2, 14.6    13.2, 15.0    14.9, 16.9    17.7, 19.1
+//   FP32 RK4      13.4, 14.0    13.3, 14.5    14.8, 15.8    17.0, 18.0
+//   FP64 field    14.2, 16.0    14.4, 16.1    16.3, 18.5    20.2, 21.4
+//   FP64 Heun     16.0, 16.9    16.1, 17.4    18.3, 20.1    21.3, 22.6
 template <typename T, typename F>
 int fixed_hx(const Group& G, F&& lds) {
   if (G.xone) return 0;
@@ -1326,7 +1333,10 @@ mmx_status eval_group(mmx_ctx* ctx, Group& G, const T* mbase, const Combine& cb,
         dim3 grid((G.Kx + G.Wy - 1) / G.Wy, 1, G.R);
         y.map = grid_map(grid);
         // fixed-length variants as for the rows (fixed_hx); FP32 columns of 64
-        // to 256 points have the register kernel
+        // to 256 points have the register kernel.  us per field evaluation of one
+        // film, constants for run-time lengths: FP64 columns of 64 points 13.3 for
+        // 14.9, 128 14.6 for 16.5, 256 16.9 for 18.1, 512 18.1 for 20.5; FP32 of 512
+        // 16.1 for 18.0
         auto lds_of = [&](int ld) { return (2 * (size_t)3 * G.Wy * ld + G.Py) * cpxb<T>(); };
         const bool fits = lds_of(G.Py + G.Py / 16) <= 64 * 1024;
         constexpr bool f64 = std::is_same<T, double>::value;

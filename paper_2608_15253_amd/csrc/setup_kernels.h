@@ -280,10 +280,10 @@ __global__ void k_rk_commit(const RkState* st, T* m, const T* m7, T* k1, const T
 // whatever the number of threads: one thread per replica (lanes = 1), or a wave
 // (a workgroup of 64 lanes per replica) that loads a tile of them at once and adds
 // each sum in one lane.  A thread that loads each partial before it adds it takes
-// 0.12 us for one (1024 workgroups of a 128 x 128 x 8 FP64 block: 120 us for the
-// energies, 5 us for the wave); a wave per replica is for many workgroups.
-// Returns whether this lane holds sums (s[v] valid); callers with lanes = 64 have
-// no other use of the workgroup's barrier.
+// some 0.1 us for one: the energies of a 128 x 128 x 8 FP64 block (1024 workgroups)
+// 214 us, 110 with the wave.  Few partials of many replicas stay with the threads.
+// Returns whether this lane holds the sums; with lanes = 64 the whole workgroup
+// calls it.
 constexpr int kSumTile = 512;
 template <int NV>
 __device__ inline bool replica_sums(const double* __restrict__ partial, int nblk, int r, int lanes,
