@@ -281,7 +281,7 @@ __global__ void k_rk_commit(const RkState* st, T* m, const T* m7, T* k1, const T
 // (a workgroup of 64 lanes per replica) that loads a tile of them at once and adds
 // each sum in one lane.  A thread that loads each partial before it adds it takes
 // some 0.1 us for one: the energies of a 128 x 128 x 8 FP64 block (1024 workgroups)
-// 214 us, 98 with the wave, of a 256 x 256 x 32 one (4096) 739 and 303.  Few partials
+// 214 us, 81 with the wave, of a 256 x 256 x 32 one (4096) 739 and 237.  Few partials
 // of many replicas stay with the threads.
 // Returns whether this lane holds the sums; with lanes = 64 the whole workgroup
 // calls it.
@@ -303,17 +303,22 @@ __device__ inline bool replica_sums(const double* __restrict__ partial, int nblk
   double acc = 0;  // lane v < NV: sum v
   for (int base = 0; base < nblk; base += kSumTile) {
     const int n = min(kSumTile, nblk - base);
+    double v[kSumTile / 64 * NV];  // a tile's loads in flight at once
+#pragma unroll
+    for (int i = 0; i < kSumTile / 64 * NV; ++i)
+      v[i] = p[(size_t)base * NV + min(t + 64 * i, n * NV - 1)];
     __syncthreads();
-    for (int i = t; i < n * NV; i += 64) tile[i] = p[(size_t)base * NV + i];
+#pragma unroll
+    for (int i = 0; i < kSumTile / 64 * NV; ++i) tile[t + 64 * i] = v[i];
     __syncthreads();
     if (t < NV) {
       int b = 0;
       for (; b + 16 <= n; b += 16) {  // sixteen reads in flight, added in order
-        double v[16];
+        double x[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = tile[(b + i) * NV + t];
+        for (int i = 0; i < 16; ++i) x[i] = tile[(b + i) * NV + t];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc += v[i];
+        for (int i = 0; i < 16; ++i) acc += x[i];
       }
       for (; b < n; ++b) acc += tile[b * NV + t];
     }
