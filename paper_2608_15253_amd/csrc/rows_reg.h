@@ -24,8 +24,8 @@
 // the transforms differs.
 // Sums of a pair computed once and the zero half of an open row left out took 12 %
 // of the vector instructions.  One film of 64 x 64: predictor 17.9 -> 16.4 us,
-// corrector 19.8 -> 18.4.  1024 films are bound by their bytes (4.3-4.4 TB/s traced, a
-// large copy 4.7) and stay where they were, 69.5 -> 68.6 and 79.0 -> 78.9.
+// corrector 19.8 -> 18.4.  1024 films are bound by their bytes (4.3 to 4.7 TB/s from
+// card to card, a large copy 4.7) and stay where they were, 69.5 -> 68.6 and 79.0 -> 78.9.
 #pragma once
 #include "common.h"
 #include "fft_lds.h"
